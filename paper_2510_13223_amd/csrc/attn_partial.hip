@@ -12,9 +12,8 @@
 // Work decomposition.  The blocks of a sequence's ranges are concatenated
 // into one virtual block sequence, mapped back to (range, logical block) by
 // a segment cursor.  Two launch shapes:
-//  * chunked: one workgroup per (chunk c, sequence b, kv head g),
-//    linearised chunk-major so that every (b, g) has its first chunk in the
-//    first wave of dispatch.  A workgroup of W wavefronts walks the virtual
+//  * chunked: one workgroup per (chunk c, sequence b, kv head g), in the order
+//    that partial_attn_kernel explains.  A workgroup of W wavefronts walks the virtual
 //    blocks of its chunk round-robin (block jr goes to wave jr % W); each
 //    wavefront keeps an online-softmax state for all G query heads of the
 //    kv head, and the W states are combined through LDS at the end.  A range
@@ -395,9 +394,14 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
   int wg = blockIdx.x - a.copies.n_wg;
   const int g = a.g0 + wg % a.ng;
   wg /= a.ng;
+  // Few pairs: a sequence's chunks one after the other, so that the chunks of a long range come as
+  // one run and spread over all CUs (chunk-major, the long range of a batch of short ones lands on
+  // every B-th workgroup and so on the same few CUs of each XCD: 4 sequences, one 15 times as long as
+  // the others, 40 us against 27).  Many pairs: chunk-major, first chunks first.
+  const int c = a.seq_major ? wg % a.nc : wg / a.B;
+  const int at = a.seq_major ? wg / a.nc : wg % a.B;
   // The dispatch order is a hint: an entry outside [0, B) is clamped, never followed.
-  const int b = a.seq_order != nullptr ? min(max(table_lookup(a.seq_order, 0, 0, wg % a.B), 0), a.B - 1) : wg % a.B;
-  const int c = wg / a.B;
+  const int b = a.seq_order != nullptr ? min(max(table_lookup(a.seq_order, 0, 0, at), 0), a.B - 1) : at;
   const int G = a.G;
   const int hq0 = g * G;
 

@@ -29,6 +29,22 @@ constexpr int kBalancedTargetWaves = 256 * 8;
 constexpr int kMinBlocksPerWave = 8;    // below this a wavefront spends more time starting than streaming
 constexpr int kMaxBlocksPerWave = 64;   // longest run of blocks one wavefront should walk (no hints)
 constexpr int kMaxChunks = 256;
+// Calls of few (sequence, kv head) pairs (make_plan).
+constexpr int kFewPairs = 1024;        // below this many active pairs (half without range hints)
+constexpr int kFewEvenGroups = 256;    // workgroups: one per CU for even ranges,
+constexpr int kFewUnknownGroups = 512; // two without range hints; with uneven ranges up to three
+constexpr int kFewUnevenGroups = 768;  // where the longest is less than twice the mean, four up to
+constexpr int kFewLongGroups = 1024;   // four times the mean, six beyond
+constexpr int kFewRaggedGroups = 1536;
+constexpr int kMinChunkBlocks = 4;     // of the longest range's chunks
+constexpr int kMinUnevenBlocks = 24;   // (block, kv head) units per workgroup on the mean: less than
+constexpr int kMinLongBlocks = 5;      // twice the mean, beyond
+constexpr int kLongChunkBlocks = 48;   // uneven chunks from here on get 8 wavefronts
+constexpr int kUnsplitBlocks = 32;     // ranges of at most this many blocks are not cut
+constexpr int kBalancedSaves = 4;
+constexpr int kBalancedLongWalk = 40;
+constexpr int64_t kSlotBytes = (kHeadDim + 1) * sizeof(float);  // a partial row and its lse
+constexpr int64_t kScratchForSplits = (int64_t)bana::kStaticScratchBytes - 4096;
 constexpr int kMaxFusedParts = 64;  // one range per lane of the segment table
 // Workgroups of an attention launch given to its side copies.  Measured on MI355X (the llama3_8b
 // layer pipeline, 4 MiB of copies beside 1 GiB of attention reads): the copies' host-memory
@@ -68,6 +84,7 @@ struct Plan {
   int waves;      // wavefronts per workgroup
   int nc;         // chunks per (sequence, kv head)
   int cmin;       // minimum blocks per chunk
+  bool seq_major; // workgroups in (sequence, chunk) order
   bool balanced;  // equal block intervals per wavefront across sequences
   int K;          // balanced: wavefronts per kv head
   int kp;         // balanced: thread groups per row of the piece merge
@@ -93,20 +110,46 @@ int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // Chunks need workspace; without it the call runs unsplit.  Without hints
 // the table width bounds the range length.
 //
+// Few pairs (below kFewPairs active (sequence, kv head) pairs, no launch-shape hints): short calls
+// wait for the chain of one workgroup -- range, table entry, first tile, its blocks one after the
+// other, the merge launch -- and longer ones for the CUs with the most blocks.  Even ranges are cut
+// into as many chunks as give one workgroup of 4 wavefronts per CU (their 8 MB of loads in flight
+// keep HBM as busy as more would).  Uneven ranges are all cut into the same number of chunks too,
+// so that a long range's are not the only ones, but into more: three, four or six workgroups per CU
+// as the longest is less than twice, up to four times or more than four times the mean, as long as
+// a workgroup keeps enough blocks on the mean.  No chunk of the longest range is below kMinChunkBlocks blocks, and ranges of at most
+// kUnsplitBlocks are not cut: there the merge launch costs more than the walk.  Measured on MI355X
+// (HIP graph of 24 calls over three inputs, us per call; the rule for many pairs -> this one):
+//   32 query / 8 kv heads  1 sequence of 256 / 1500 / 6000 tokens  6.5 -> 5.3, 15.9 -> 8.9, 18.0 -> 11.0
+//                          4 sequences of 700 / 3000               11.5 -> 8.8, 18.5 -> 14
+//                          48 sequences of 800                     33 -> 28
+//   64 / 8                 12 log-normal around 6000 (balanced)    71.5 -> 66
+//   28 / 4                 16 log-normal around 6000 (balanced)    54.5 -> 49
+// (even ranges at two workgroups per CU: 3 % slower or more, at half a workgroup 4 to 20 %; from 1024
+// pairs on the rule for many pairs gives one chunk of as many wavefronts).
+//
 // Balanced launch (batch <= kMaxBalancedBatch): kBalancedTargetWaves
 // wavefronts split over the kv heads, each over an equal interval of the
 // call's blocks in sequence order, the pieces of a sequence merged
 // afterwards.  Chosen when the ranges are uneven (longest > 1.25 x the mean),
 // the active (sequence, kv head) pairs number at most a quarter of a round's
-// wavefronts and the call has at least kMinBlocksPerWave blocks per
-// wavefront (or asked for by plan_hint 2): there the chunked plan has to
-// round every range to whole chunks within one or two rounds.  With even
-// ranges that rounding costs less than the piece merge, and with many pairs
+// wavefronts and either the wavefronts of the chunked plan's longest chunk (8 to
+// a workgroup) would walk at least kBalancedSaves blocks more than the balanced
+// launch's, or those walk kBalancedLongWalk blocks or more, which makes its
+// merge cheap, or, in a long call, most sequences have no range, whose chunk
+// rows the chunked plan's merge would read all the same (54 of 256 with a
+// range: 73 us and a merge of 6, chunked 78 and 9); or asked for by plan_hint 2.  With even ranges the piece merge
+// costs more than the rounding to whole chunks, and with many pairs
 // several dispatch rounds, longest range first, balance by themselves
 // (measured on MI355X, cold caches: mixed's 2048-pair calls 193 / 251 us
 // chunked against 214 / 263 us balanced; its 1024-pair head halves 317
 // against 278 us; long's fused call, 1.3 x spread, 494 against 478 us).
-Plan make_plan(const bana_dims* d) {
+// kBalancedSaves: log-normal lengths, blocks saved and us chunked / balanced:
+// -6 49 / 54, -2 92 / 95, 1 91 / 86, 3 107 / 103, 14 125 / 107.
+//
+// split: whether the call has workspace for the plan.  Without it every range
+// stays in one workgroup, which then wants as many wavefronts as it can use.
+Plan make_plan(const bana_dims* d, bool split = true) {
   const int64_t pairs = (int64_t)d->batch * d->num_kv_heads;
   const int64_t active = d->nonempty_ranges > 0 ? std::min<int64_t>(d->nonempty_ranges, d->batch) : d->batch;
   const int64_t active_pairs = active * d->num_kv_heads;
@@ -123,8 +166,17 @@ Plan make_plan(const bana_dims* d) {
       hinted ? std::max<int64_t>(1, std::min<int64_t>(bound + 1, d->total_range_tokens / (kBlockSize * active) + 1))
              : bound;
   const bool uneven = hinted && 4 * bound > 5 * mean_blocks;
+  int64_t few_groups = hinted ? kFewEvenGroups : kFewUnknownGroups;
+  if (uneven) {
+    const int64_t units = mean_blocks * active_pairs;
+    const int64_t groups = bound < 2 * mean_blocks    ? std::min<int64_t>(units / kMinUnevenBlocks, kFewUnevenGroups)
+                           : bound <= 4 * mean_blocks ? std::min<int64_t>(units / kMinLongBlocks, kFewLongGroups)
+                                                      : std::min<int64_t>(units / kMinLongBlocks, kFewRaggedGroups);
+    few_groups = std::max<int64_t>(kFewEvenGroups, groups);
+  }
   Plan p;
   p.balanced = false;
+  p.seq_major = false;
   // The dispatch order pays off only when ranges are uneven (long ones first, short ones
   // filling the end of the launch); with even or unknown lengths its lookup would add one
   // dependent load to every wavefront's start, so it is skipped.
@@ -133,11 +185,21 @@ Plan make_plan(const bana_dims* d) {
   p.kp = 1;
   // The balanced schedule counts the blocks of all ranges of all sequences in 32 bits.
   const bool fits32 = (int64_t)d->batch * kMaxFusedParts * d->max_blocks_per_seq <= INT32_MAX;
-  if (d->batch <= bana::kMaxBalancedBatch && fits32 && d->waves_hint == 0 && d->chunks_hint == 0 &&
+  if (split && d->batch <= bana::kMaxBalancedBatch && fits32 && d->waves_hint == 0 && d->chunks_hint == 0 &&
       d->plan_hint != 1) {
     const int64_t call_blocks = hinted ? d->total_range_tokens / kBlockSize + active : 0;
     const bool few_pairs = 4 * active_pairs <= kTargetWaves;
-    p.balanced = d->plan_hint == 2 || (uneven && few_pairs && call_blocks >= (int64_t)kMinBlocksPerWave * p.K);
+    // Blocks the wavefronts of the longest chunk walk, and those of the balanced launch.
+    const int64_t chunked_walk = bound / (8 * std::max<int64_t>(1, few_groups / active_pairs));
+    const int64_t balanced_walk = call_blocks * d->num_kv_heads / kBalancedTargetWaves;
+    // Short calls take it only with slots that the static scratch holds too.
+    const bool long_call = call_blocks >= (int64_t)kMinBlocksPerWave * p.K;
+    const bool long_or_fits = long_call ||
+                              ((int64_t)p.K + d->batch) * d->num_q_heads * kSlotBytes <= kScratchForSplits;
+    p.balanced = d->plan_hint == 2 ||
+                 (uneven && few_pairs && long_or_fits &&
+                  (chunked_walk >= balanced_walk + kBalancedSaves || balanced_walk >= kBalancedLongWalk ||
+                   (2 * active < d->batch && long_call)));
   }
   if (p.balanced) {
     // Pieces of the row with the most: its blocks over intervals of at least s_lo blocks, plus
@@ -158,8 +220,22 @@ Plan make_plan(const bana_dims* d) {
     p.cmin = 1;
     return p;
   }
+  const bool few = d->waves_hint == 0 && d->chunks_hint == 0 && active_pairs < (hinted ? kFewPairs : kFewPairs / 2);
+  int64_t few_chunks = 1;
+  if (few && split && bound > kUnsplitBlocks) {
+    few_chunks = std::min<int64_t>(few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks));
+    // Without hints no wavefront walks more than kMaxBlocksPerWave blocks.
+    if (!hinted) few_chunks = std::max<int64_t>(few_chunks, ceil_div(bound, 8 * kMaxBlocksPerWave));
+    // Few active sequences of a large batch: keep the chunk partials of all of it small.
+    few_chunks = std::min<int64_t>(few_chunks, kScratchForSplits / ((int64_t)d->batch * d->num_q_heads * kSlotBytes));
+    few_chunks = std::max<int64_t>(few_chunks, 1);
+  }
   if (d->waves_hint > 0)
     p.waves = d->waves_hint;
+  else if (few && bound <= kUnsplitBlocks)
+    p.waves = bound <= kUnsplitBlocks / 2 ? 4 : 8;
+  else if (few)
+    p.waves = !split || (uneven && bound >= kLongChunkBlocks * few_chunks) ? 8 : 4;
   else if (uneven && bound >= 8 * kMinBlocksPerWave)
     p.waves = 8;
   else
@@ -171,6 +247,10 @@ Plan make_plan(const bana_dims* d) {
   if (d->chunks_hint > 0) {
     p.nc = d->chunks_hint;
     p.cmin = 1;
+  } else if (few) {
+    p.nc = (int)few_chunks;
+    p.cmin = 1;
+    p.seq_major = true;
   } else if (hinted) {
     // (block, kv head) units of the call and the blocks per wavefront if they
     // were spread evenly over one round of resident wavefronts.
@@ -194,7 +274,7 @@ Plan make_plan(const bana_dims* d) {
     p.nc = std::max(ceil_div(wpp, p.waves), ceil_div(bound, (int64_t)p.waves * kMaxBlocksPerWave));
     p.cmin = p.waves * 16;
   }
-  p.nc = std::max(1, std::min(p.nc, kMaxChunks));
+  p.nc = split ? std::max(1, std::min(p.nc, kMaxChunks)) : 1;
   if (((int64_t)p.nc * pairs + kMaxSideCopyGroups) * 64 * p.waves > kMaxLaunchItems) p.nc = 1;
   return p;
 }
@@ -274,13 +354,7 @@ bana_status run_attention(const bana_dims* d, const void* q, const void* k_cache
   sub.num_q_heads = ng * G;
   Plan plan = make_plan(&sub);
   const WorkspaceLayout ws = layout_for(&sub, plan);
-  if (ws.total > 0 && (workspace == nullptr || workspace_bytes < ws.total)) {
-    if (plan.balanced) {  // the chunked plan's launch shape, unsplit
-      sub.plan_hint = 1;
-      plan = make_plan(&sub);
-    }
-    plan.nc = 1;
-  }
+  if (ws.total > 0 && (workspace == nullptr || workspace_bytes < ws.total)) plan = make_plan(&sub, false);
 
   bana::PartialArgs a;
   a.q = static_cast<const uint16_t*>(q);
@@ -300,6 +374,7 @@ bana_status run_attention(const bana_dims* d, const void* q, const void* k_cache
   a.ng = ng;
   a.nc = plan.nc;
   a.cmin = plan.cmin;
+  a.seq_major = plan.seq_major;
   // Workspace partials hold the call's heads only; merged rows go to their place in out / lse.
   a.out_hq = ng * G;
   a.out_h0 = g0 * G;

@@ -1,0 +1,83 @@
+"""Launch shapes of calls with few (sequence, kv head) pairs: where a range starts to be cut, where the
+number of workgroups per CU changes, and the limits of the chunk partials.
+
+GPU cases are held to the fp64 oracle (max-abs 2e-3, rel-L2 1e-3, |dlse| 1e-4, the library's stated bar)
+per partition, merged and fused; the plans are checked on the host through the workspace they ask for.
+"""
+
+import ctypes
+import math
+
+import pytest
+
+from paper_2510_13223_amd import bana, workloads as W
+
+ROW_BYTES = 129 * 4  # a chunk's output row and lse
+
+
+def _chunks(B, Hq, Hkv, longest, total, **kw):
+    d = bana.make_dims(B, Hq, Hkv, 8192, 100000, max_range_tokens=longest, total_range_tokens=total, **kw)
+    ws = bana.lib().bana_decode_attn_workspace_bytes(ctypes.byref(d))
+    return max(1, round(ws / (B * Hq * ROW_BYTES))), ws
+
+
+def test_ranges_of_up_to_32_blocks_are_not_cut():
+    for B, Hkv in ((1, 1), (1, 8), (8, 2), (31, 8)):
+        assert _chunks(B, 4 * Hkv, Hkv, 512, 512 * B) == (1, 0)
+        assert _chunks(B, 4 * Hkv, Hkv, 528, 528 * B)[0] == (9 if B * Hkv <= 16 else 1)
+
+
+def test_even_ranges_get_one_workgroup_per_cu():
+    for B, Hkv in ((1, 2), (3, 8), (16, 8), (32, 8), (33, 8), (100, 8)):
+        n, _ = _chunks(B, 4 * Hkv, Hkv, 100000, 100000 * B)
+        assert n == max(1, 256 // (B * Hkv)), (B, Hkv)
+
+
+def test_chunk_partials_of_short_calls_fit_the_static_scratch():
+    """Few sequences with a range in a large batch: the no-allocation call keeps accepting them."""
+    for B in (2, 64, 500, 2048, 20000):
+        for active in (1, 2, 5, 60):
+            if active > B:
+                continue
+            for Hq, Hkv in ((8, 2), (64, 8), (128, 8)):
+                for longest in (600, 8000, 120000):
+                    for total in (longest * active, longest + 100 * (active - 1)):
+                        _, ws = _chunks(B, Hq, Hkv, longest, total, nonempty_ranges=active, plan_hint=1)
+                        assert ws <= bana.STATIC_SCRATCH_BYTES, (B, active, Hq, longest, total)
+
+
+GPU_CASES = [
+    # B, Hq, Hkv, lengths (cycled), parts
+    (1, 4, 1, [256], 1),          # a whole range per workgroup: 16 blocks, 4 wavefronts
+    (1, 16, 1, [257], 1),         # 17 blocks, 8 wavefronts
+    (3, 8, 2, [512, 511, 500], 1),
+    (3, 8, 2, [513, 514, 528], 2),  # 33 blocks: cut, one block per wavefront
+    (1, 2, 2, [5000], 2),         # 128 chunks allowed, 79 used
+    (17, 32, 16, [700], 1),       # 272 pairs: one chunk
+    (16, 32, 16, [700, 690], 1),  # 256 pairs
+    (5, 8, 4, [4000, 2500, 2600, 2500, 2500], 2),   # longest below twice the mean
+    (6, 32, 8, [6000, 900, 1200, 800, 1, 900], 1),  # up to four times
+    (9, 16, 1, [9000, 300, 17, 40, 200, 600, 5, 90, 333], 3),  # beyond, group of 16
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(GPU_CASES)))
+def test_short_call_shapes_match_the_oracle(case):
+    from test_gpu_parity import _full_parity
+
+    B, Hq, Hkv, cycle, parts = GPU_CASES[case]
+    lens = [cycle[b % len(cycle)] for b in range(B)]
+    # Cuts at any token; the ranges cover the sequence, as the helper expects; parts of short ones are empty.
+    ranges = [[(L * p // parts, L * (p + 1) // parts) for L in lens] for p in range(parts)]
+    w = W.make_custom(900 + case, B, Hq, Hkv, lens, ranges, q_scale=1 / math.sqrt(128))
+    for kw in ({}, {"range_hints": False}, {"order_hints": False, "plan_hint": 1}, {"use_workspace": False}):
+        _full_parity(w, **kw)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [5, 8, 16, 17, 33, 96])
+def test_merge_of_few_rows_at_its_edges(n):
+    from test_gpu_parity import test_merge_matches_oracle_merge
+
+    test_merge_matches_oracle_merge(n, 3, 8)
