@@ -1,8 +1,10 @@
-"""Python binding of libbana.so (ctypes).
+"""Python binding of libbana.so (ctypes, with native argument checks).
 
 Argument marshalling only: every function checks tensor dtypes, shapes,
 devices and contiguity, then passes raw device pointers and the HIP stream
-handle to the C ABI declared in ``include/bana.h``.  All arithmetic runs in
+handle to the C ABI declared in ``include/bana.h``.  The calls of a decode
+step make these checks in ``_native`` (csrc/binding.cpp); where it finds
+anything not as wanted, the checks below run and say what.  All arithmetic runs in
 the library's HIP kernels; there is no fallback path, and a missing library
 raises.  PyTorch only provides device memory and streams.
 """
@@ -63,6 +65,27 @@ class BanaError(RuntimeError):
 
 
 _lib = None
+_native = None
+
+
+def _calls():
+    """The native checks-and-calls module, set up with the addresses of the loaded library."""
+    global _native
+    if _native is None:
+        L = lib()
+        try:
+            from . import _native as n
+        except ImportError as e:
+            raise RuntimeError("the native binding is missing: build it with "
+                               "`python -m paper_2510_13223_amd.build`") from e
+        names = ("decode_attn_partial", "decode_attn_partial_noalloc", "decode_attn_fused", "decode_attn_fused_copies",
+                 "decode_attn_heads", "merge_partials", "migrate_kv_blocks")
+        size = n.setup(tuple(ctypes.cast(getattr(L, "bana_" + name), ctypes.c_void_p).value for name in names),
+                       torch._C._cuda_getCurrentRawStream, torch.cuda.Stream, bana_dims)
+        if size != ctypes.sizeof(bana_dims):
+            raise RuntimeError("the native binding was built with another bana_dims")
+        _native = n
+    return _native
 
 
 def lib() -> ctypes.CDLL:
@@ -196,23 +219,26 @@ def bana_decode_attn_partial(q, k_cache, v_cache, block_table, seq_lens, kv_rang
                              out_partial, lse, workspace: Optional[torch.Tensor] = None, stream=None,
                              dims: Optional[bana_dims] = None, max_range_tokens: int = 0) -> None:
     """Partial attention of one partition; see ``bana_decode_attn_partial`` in include/bana.h."""
-    B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
-    _need(kv_range_begin, "kv_range_begin", torch.int32, (B,))
-    _need(kv_range_end, "kv_range_end", torch.int32, (B,))
-    _need(out_partial, "out_partial", torch.float32, (B, Hq, D))
-    _need(lse, "lse", torch.float32, (B, Hq))
-    _same_device(q, kv_range_begin, kv_range_end, out_partial, lse, workspace)
-    ws_bytes = 0
-    if workspace is not None:
-        _need(workspace, "workspace", workspace.dtype)
-        ws_bytes = workspace.numel() * workspace.element_size()
-    if dims is None:
-        dims = dims_for(q, k_cache, block_table, max_range_tokens)
-    _check_dims(dims, q, k_cache, block_table)
-    st = lib().bana_decode_attn_partial(
-        ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
-        _ptr(kv_range_begin), _ptr(kv_range_end), _ptr(out_partial), _ptr(lse), _ptr(workspace), ws_bytes,
-        _stream(stream))
+    st = _calls().partial(q, k_cache, v_cache, block_table, seq_lens, kv_range_begin, kv_range_end, out_partial, lse,
+                          workspace, stream, dims, max_range_tokens)
+    if st is None:
+        B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
+        _need(kv_range_begin, "kv_range_begin", torch.int32, (B,))
+        _need(kv_range_end, "kv_range_end", torch.int32, (B,))
+        _need(out_partial, "out_partial", torch.float32, (B, Hq, D))
+        _need(lse, "lse", torch.float32, (B, Hq))
+        _same_device(q, kv_range_begin, kv_range_end, out_partial, lse, workspace)
+        ws_bytes = 0
+        if workspace is not None:
+            _need(workspace, "workspace", workspace.dtype)
+            ws_bytes = workspace.numel() * workspace.element_size()
+        if dims is None:
+            dims = dims_for(q, k_cache, block_table, max_range_tokens)
+        _check_dims(dims, q, k_cache, block_table)
+        st = lib().bana_decode_attn_partial(
+            ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
+            _ptr(kv_range_begin), _ptr(kv_range_end), _ptr(out_partial), _ptr(lse), _ptr(workspace), ws_bytes,
+            _stream(stream))
     if st != BANA_OK:
         raise BanaError(st, "bana_decode_attn_partial")
 
@@ -226,18 +252,21 @@ def bana_decode_attn_partial_noalloc(q, k_cache, v_cache, block_table, seq_lens,
     """``bana_decode_attn_partial`` with the library's static device scratch in place of a workspace
     (for callers that cannot allocate); see ``bana_decode_attn_partial_noalloc`` in include/bana.h.
     Calls that may overlap on one device share that scratch and must be serialised."""
-    B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
-    _need(kv_range_begin, "kv_range_begin", torch.int32, (B,))
-    _need(kv_range_end, "kv_range_end", torch.int32, (B,))
-    _need(out_partial, "out_partial", torch.float32, (B, Hq, D))
-    _need(lse, "lse", torch.float32, (B, Hq))
-    _same_device(q, kv_range_begin, kv_range_end, out_partial, lse)
-    if dims is None:
-        dims = dims_for(q, k_cache, block_table, max_range_tokens)
-    _check_dims(dims, q, k_cache, block_table)
-    st = lib().bana_decode_attn_partial_noalloc(
-        ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
-        _ptr(kv_range_begin), _ptr(kv_range_end), _ptr(out_partial), _ptr(lse), _stream(stream))
+    st = _calls().noalloc(q, k_cache, v_cache, block_table, seq_lens, kv_range_begin, kv_range_end, out_partial, lse,
+                          stream, dims, max_range_tokens)
+    if st is None:
+        B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
+        _need(kv_range_begin, "kv_range_begin", torch.int32, (B,))
+        _need(kv_range_end, "kv_range_end", torch.int32, (B,))
+        _need(out_partial, "out_partial", torch.float32, (B, Hq, D))
+        _need(lse, "lse", torch.float32, (B, Hq))
+        _same_device(q, kv_range_begin, kv_range_end, out_partial, lse)
+        if dims is None:
+            dims = dims_for(q, k_cache, block_table, max_range_tokens)
+        _check_dims(dims, q, k_cache, block_table)
+        st = lib().bana_decode_attn_partial_noalloc(
+            ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
+            _ptr(kv_range_begin), _ptr(kv_range_end), _ptr(out_partial), _ptr(lse), _stream(stream))
     if st != BANA_OK:
         text = lib().bana_last_error().decode()
         raise BanaError(st, "bana_decode_attn_partial_noalloc",
@@ -274,26 +303,29 @@ def bana_decode_attn_fused(q, k_cache, v_cache, block_table, seq_lens, kv_range_
                            workspace: Optional[torch.Tensor] = None, stream=None,
                            dims: Optional[bana_dims] = None) -> None:
     """All partitions ``kv_range_begin/end [n_parts, B]`` and their merge in one launch; see include/bana.h."""
-    B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
-    if kv_range_begin.dim() != 2 or kv_range_begin.shape[1] != B:
-        raise ValueError("kv_range_begin must be [n_parts, B]")
-    n = kv_range_begin.shape[0]
-    _need(kv_range_begin, "kv_range_begin", torch.int32, (n, B))
-    _need(kv_range_end, "kv_range_end", torch.int32, (n, B))
-    _need(out, "out", torch.float32, (B, Hq, D))
-    _need(lse_out, "lse_out", torch.float32, (B, Hq))
-    _same_device(q, kv_range_begin, kv_range_end, out, lse_out, workspace)
-    ws_bytes = 0
-    if workspace is not None:
-        _need(workspace, "workspace", workspace.dtype)
-        ws_bytes = workspace.numel() * workspace.element_size()
-    if dims is None:
-        dims = dims_for(q, k_cache, block_table)
-    _check_dims(dims, q, k_cache, block_table)
-    st = lib().bana_decode_attn_fused(
-        ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
-        _ptr(kv_range_begin), _ptr(kv_range_end), n, _ptr(out), _ptr(lse_out), _ptr(workspace), ws_bytes,
-        _stream(stream))
+    st = _calls().fused(q, k_cache, v_cache, block_table, seq_lens, kv_range_begin, kv_range_end, out, lse_out,
+                        workspace, stream, dims, None)
+    if st is None:
+        B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
+        if kv_range_begin.dim() != 2 or kv_range_begin.shape[1] != B:
+            raise ValueError("kv_range_begin must be [n_parts, B]")
+        n = kv_range_begin.shape[0]
+        _need(kv_range_begin, "kv_range_begin", torch.int32, (n, B))
+        _need(kv_range_end, "kv_range_end", torch.int32, (n, B))
+        _need(out, "out", torch.float32, (B, Hq, D))
+        _need(lse_out, "lse_out", torch.float32, (B, Hq))
+        _same_device(q, kv_range_begin, kv_range_end, out, lse_out, workspace)
+        ws_bytes = 0
+        if workspace is not None:
+            _need(workspace, "workspace", workspace.dtype)
+            ws_bytes = workspace.numel() * workspace.element_size()
+        if dims is None:
+            dims = dims_for(q, k_cache, block_table)
+        _check_dims(dims, q, k_cache, block_table)
+        st = lib().bana_decode_attn_fused(
+            ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
+            _ptr(kv_range_begin), _ptr(kv_range_end), n, _ptr(out), _ptr(lse_out), _ptr(workspace), ws_bytes,
+            _stream(stream))
     if st != BANA_OK:
         raise BanaError(st, "bana_decode_attn_fused")
 
@@ -319,27 +351,31 @@ def bana_decode_attn_fused_copies(q, k_cache, v_cache, block_table, seq_lens, kv
                                   lse_out, copies=(), workspace: Optional[torch.Tensor] = None, stream=None,
                                   dims: Optional[bana_dims] = None) -> None:
     """The fused call with up to 8 (dst, src) copies carried by the same launch; see include/bana.h."""
-    B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
-    if kv_range_begin.dim() != 2 or kv_range_begin.shape[1] != B:
-        raise ValueError("kv_range_begin must be [n_parts, B]")
-    n = kv_range_begin.shape[0]
-    _need(kv_range_begin, "kv_range_begin", torch.int32, (n, B))
-    _need(kv_range_end, "kv_range_end", torch.int32, (n, B))
-    _need(out, "out", torch.float32, (B, Hq, D))
-    _need(lse_out, "lse_out", torch.float32, (B, Hq))
-    _same_device(q, kv_range_begin, kv_range_end, out, lse_out, workspace)
-    ws_bytes = 0
-    if workspace is not None:
-        _need(workspace, "workspace", workspace.dtype)
-        ws_bytes = workspace.numel() * workspace.element_size()
-    if dims is None:
-        dims = dims_for(q, k_cache, block_table)
-    _check_dims(dims, q, k_cache, block_table)
-    arr = copy_list(list(copies))
-    st = lib().bana_decode_attn_fused_copies(
-        ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
-        _ptr(kv_range_begin), _ptr(kv_range_end), n, _ptr(out), _ptr(lse_out), _ptr(workspace), ws_bytes, arr,
-        len(arr), _stream(stream))
+    copies = list(copies)
+    st = _calls().fused(q, k_cache, v_cache, block_table, seq_lens, kv_range_begin, kv_range_end, out, lse_out,
+                        workspace, stream, dims, copies)
+    if st is None:
+        B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
+        if kv_range_begin.dim() != 2 or kv_range_begin.shape[1] != B:
+            raise ValueError("kv_range_begin must be [n_parts, B]")
+        n = kv_range_begin.shape[0]
+        _need(kv_range_begin, "kv_range_begin", torch.int32, (n, B))
+        _need(kv_range_end, "kv_range_end", torch.int32, (n, B))
+        _need(out, "out", torch.float32, (B, Hq, D))
+        _need(lse_out, "lse_out", torch.float32, (B, Hq))
+        _same_device(q, kv_range_begin, kv_range_end, out, lse_out, workspace)
+        ws_bytes = 0
+        if workspace is not None:
+            _need(workspace, "workspace", workspace.dtype)
+            ws_bytes = workspace.numel() * workspace.element_size()
+        if dims is None:
+            dims = dims_for(q, k_cache, block_table)
+        _check_dims(dims, q, k_cache, block_table)
+        arr = copy_list(copies)
+        st = lib().bana_decode_attn_fused_copies(
+            ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
+            _ptr(kv_range_begin), _ptr(kv_range_end), n, _ptr(out), _ptr(lse_out), _ptr(workspace), ws_bytes, arr,
+            len(arr), _stream(stream))
     if st != BANA_OK:
         raise BanaError(st, "bana_decode_attn_fused_copies")
 
@@ -351,41 +387,46 @@ def bana_decode_attn_heads(q, k_cache, v_cache, block_table, seq_lens, kv_range_
 
     The workspace is sized by ``bana_decode_attn_workspace_bytes(head_range_dims(dims, begin, end))``.
     """
-    B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
-    _need(kv_range_begin, "kv_range_begin", torch.int32, (B,))
-    _need(kv_range_end, "kv_range_end", torch.int32, (B,))
-    _need(out, "out", torch.float32, (B, Hq, D))
-    _need(lse, "lse", torch.float32, (B, Hq))
-    _same_device(q, kv_range_begin, kv_range_end, out, lse, workspace)
-    ws_bytes = 0
-    if workspace is not None:
-        _need(workspace, "workspace", workspace.dtype)
-        ws_bytes = workspace.numel() * workspace.element_size()
-    if dims is None:
-        dims = dims_for(q, k_cache, block_table)
-    _check_dims(dims, q, k_cache, block_table)
-    st = lib().bana_decode_attn_heads(
-        ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
-        _ptr(kv_range_begin), _ptr(kv_range_end), int(kv_head_begin), int(kv_head_end), _ptr(out), _ptr(lse),
-        _ptr(workspace), ws_bytes, _stream(stream))
+    st = _calls().heads(q, k_cache, v_cache, block_table, seq_lens, kv_range_begin, kv_range_end, kv_head_begin,
+                        kv_head_end, out, lse, workspace, stream, dims)
+    if st is None:
+        B, Hq, D = _check_attn_inputs(q, k_cache, v_cache, block_table, seq_lens)
+        _need(kv_range_begin, "kv_range_begin", torch.int32, (B,))
+        _need(kv_range_end, "kv_range_end", torch.int32, (B,))
+        _need(out, "out", torch.float32, (B, Hq, D))
+        _need(lse, "lse", torch.float32, (B, Hq))
+        _same_device(q, kv_range_begin, kv_range_end, out, lse, workspace)
+        ws_bytes = 0
+        if workspace is not None:
+            _need(workspace, "workspace", workspace.dtype)
+            ws_bytes = workspace.numel() * workspace.element_size()
+        if dims is None:
+            dims = dims_for(q, k_cache, block_table)
+        _check_dims(dims, q, k_cache, block_table)
+        st = lib().bana_decode_attn_heads(
+            ctypes.byref(dims), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(seq_lens),
+            _ptr(kv_range_begin), _ptr(kv_range_end), int(kv_head_begin), int(kv_head_end), _ptr(out), _ptr(lse),
+            _ptr(workspace), ws_bytes, _stream(stream))
     if st != BANA_OK:
         raise BanaError(st, "bana_decode_attn_heads")
 
 
 def bana_merge_partials(out_partials, lses, out, lse_out: Optional[torch.Tensor] = None, stream=None) -> None:
     """Log-sum-exp merge of ``out_partials [n_parts, B, Hq, D]`` / ``lses [n_parts, B, Hq]``."""
-    if out_partials.dim() != 4:
-        raise ValueError("out_partials must be [n_parts, B, Hq, D]")
-    n, B, Hq, D = out_partials.shape
-    _need(out_partials, "out_partials", torch.float32)
-    _need(lses, "lses", torch.float32, (n, B, Hq))
-    _need(out, "out", torch.float32, (B, Hq, D))
-    if lse_out is not None:
-        _need(lse_out, "lse_out", torch.float32, (B, Hq))
-    _same_device(out_partials, lses, out, lse_out)
-    dims = bana_dims(B, Hq, 1, D, BLOCK_SIZE, 1, 1, 0, 0, 0, 0, 0)
-    st = lib().bana_merge_partials(ctypes.byref(dims), _ptr(out_partials), _ptr(lses), n, _ptr(out), _ptr(lse_out),
-                                   _stream(stream))
+    st = _calls().merge(out_partials, lses, out, lse_out, stream)
+    if st is None:
+        if out_partials.dim() != 4:
+            raise ValueError("out_partials must be [n_parts, B, Hq, D]")
+        n, B, Hq, D = out_partials.shape
+        _need(out_partials, "out_partials", torch.float32)
+        _need(lses, "lses", torch.float32, (n, B, Hq))
+        _need(out, "out", torch.float32, (B, Hq, D))
+        if lse_out is not None:
+            _need(lse_out, "lse_out", torch.float32, (B, Hq))
+        _same_device(out_partials, lses, out, lse_out)
+        dims = bana_dims(B, Hq, 1, D, BLOCK_SIZE, 1, 1, 0, 0, 0, 0, 0)
+        st = lib().bana_merge_partials(ctypes.byref(dims), _ptr(out_partials), _ptr(lses), n, _ptr(out), _ptr(lse_out),
+                                       _stream(stream))
     if st != BANA_OK:
         raise BanaError(st, "bana_merge_partials")
 
@@ -393,24 +434,27 @@ def bana_merge_partials(out_partials, lses, out, lse_out: Optional[torch.Tensor]
 def bana_migrate_kv_blocks(src_k, src_v, src_table, dst_k, dst_v, dst_table, blk_begin, blk_end, stream=None,
                            max_range_tokens: int = 0) -> None:
     """Copy the K/V tiles of logical blocks [blk_begin, blk_end) between pools; see include/bana.h."""
-    if src_k.dim() != 5 or dst_k.dim() != 5:
-        raise ValueError("k pools must be [num_blocks, Hkv, D / 8, block_size, 8]")
-    nb, Hkv, _, bs, _ = src_k.shape
-    nbd = dst_k.shape[0]
-    B, mb = src_table.shape
-    _need(src_k, "src_k", torch.bfloat16, (nb, Hkv, HEAD_DIM // 8, bs, 8))
-    _need(src_v, "src_v", torch.bfloat16, (nb, Hkv, HEAD_DIM, bs))
-    _need(dst_k, "dst_k", torch.bfloat16, (nbd, Hkv, HEAD_DIM // 8, bs, 8))
-    _need(dst_v, "dst_v", torch.bfloat16, (nbd, Hkv, HEAD_DIM, bs))
-    _need(src_table, "src_table", torch.int32, (B, mb))
-    _need(dst_table, "dst_table", torch.int32, (B, mb))
-    _need(blk_begin, "blk_begin", torch.int32, (B,))
-    _need(blk_end, "blk_end", torch.int32, (B,))
-    _same_device(src_k, src_v, src_table, dst_k, dst_v, dst_table, blk_begin, blk_end)
-    dims = bana_dims(B, Hkv, Hkv, HEAD_DIM, bs, mb, nb, max_range_tokens, 0, 0, 0, 0)
-    st = lib().bana_migrate_kv_blocks(ctypes.byref(dims), _ptr(src_k), _ptr(src_v), _ptr(src_table), _ptr(dst_k),
-                                      _ptr(dst_v), _ptr(dst_table), nbd, _ptr(blk_begin), _ptr(blk_end),
-                                      _stream(stream))
+    st = _calls().migrate(src_k, src_v, src_table, dst_k, dst_v, dst_table, blk_begin, blk_end, stream,
+                          max_range_tokens)
+    if st is None:
+        if src_k.dim() != 5 or dst_k.dim() != 5:
+            raise ValueError("k pools must be [num_blocks, Hkv, D / 8, block_size, 8]")
+        nb, Hkv, _, bs, _ = src_k.shape
+        nbd = dst_k.shape[0]
+        B, mb = src_table.shape
+        _need(src_k, "src_k", torch.bfloat16, (nb, Hkv, HEAD_DIM // 8, bs, 8))
+        _need(src_v, "src_v", torch.bfloat16, (nb, Hkv, HEAD_DIM, bs))
+        _need(dst_k, "dst_k", torch.bfloat16, (nbd, Hkv, HEAD_DIM // 8, bs, 8))
+        _need(dst_v, "dst_v", torch.bfloat16, (nbd, Hkv, HEAD_DIM, bs))
+        _need(src_table, "src_table", torch.int32, (B, mb))
+        _need(dst_table, "dst_table", torch.int32, (B, mb))
+        _need(blk_begin, "blk_begin", torch.int32, (B,))
+        _need(blk_end, "blk_end", torch.int32, (B,))
+        _same_device(src_k, src_v, src_table, dst_k, dst_v, dst_table, blk_begin, blk_end)
+        dims = bana_dims(B, Hkv, Hkv, HEAD_DIM, bs, mb, nb, max_range_tokens, 0, 0, 0, 0)
+        st = lib().bana_migrate_kv_blocks(ctypes.byref(dims), _ptr(src_k), _ptr(src_v), _ptr(src_table), _ptr(dst_k),
+                                          _ptr(dst_v), _ptr(dst_table), nbd, _ptr(blk_begin), _ptr(blk_end),
+                                          _stream(stream))
     if st != BANA_OK:
         raise BanaError(st, "bana_migrate_kv_blocks")
 

@@ -81,7 +81,33 @@ def build_timeline(verbose: bool = False) -> str:
     return build(verbose, out=TIMELINE_LIB, defines=("BANA_WAVE_TIMELINE",))
 
 
+NATIVE = os.path.join(PKG, "_native.so")
+
+
+def build_native(verbose: bool = False) -> str:
+    """The Python binding's native argument checks (csrc/binding.cpp, host code: g++, Python and torch headers)."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = NATIVE + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{sysconfig.get_paths()['include']}", *[f"-I{p}" for p in include_paths()], f"-I{INCLUDE}",
+           os.path.join(CSRC, "binding.cpp"), f"-L{libs}", "-lc10", "-ltorch_cpu", "-ltorch_python", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for binding.cpp:\n{r.stderr}")
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 if __name__ == "__main__":
     print(build(verbose="-v" in sys.argv))
+    print(build_native(verbose="-v" in sys.argv))
     print(build_racecheck(verbose="-v" in sys.argv))
     print(build_timeline(verbose="-v" in sys.argv))
