@@ -391,15 +391,20 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     return;
   }
   BANA_TIMELINE_MARK(0);
-  int wg = blockIdx.x - a.copies.n_wg;
-  const int g = a.g0 + wg % a.ng;
-  wg /= a.ng;
+  const unsigned wg = blockIdx.x - a.copies.n_wg;
+  const unsigned bc = a.by_ng.quotient(wg);  // (sequence, chunk)
+  const int g = a.g0 + (int)(wg - bc * a.ng);
   // Few pairs: a sequence's chunks one after the other, so that the chunks of a long range come as
   // one run and spread over all CUs (chunk-major, the long range of a batch of short ones lands on
   // every B-th workgroup and so on the same few CUs of each XCD: 4 sequences, one 15 times as long as
   // the others, 40 us against 27).  Many pairs: chunk-major, first chunks first.
-  const int c = a.seq_major ? wg % a.nc : wg / a.B;
-  const int at = a.seq_major ? wg / a.nc : wg % a.B;
+  int c = 0, at = (int)bc;
+  if (a.nc > 1) {
+    const unsigned hi = (a.seq_major ? a.by_nc : a.by_B).quotient(bc);
+    const int lo = (int)(bc - hi * (a.seq_major ? a.nc : a.B));
+    c = a.seq_major ? lo : (int)hi;
+    at = a.seq_major ? (int)hi : lo;
+  }
   // The dispatch order is a hint: an entry outside [0, B) is clamped, never followed.
   const int b = a.seq_order != nullptr ? min(max(table_lookup(a.seq_order, 0, 0, at), 0), a.B - 1) : at;
   const int G = a.G;
@@ -409,16 +414,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
   sg.load(a, b, lane, n_parts);
   const int nblk = sg.total(n_parts);
   BANA_TIMELINE_MARK(1);
-  int per = (nblk + a.nc - 1) / a.nc;
-  if (per < a.cmin) per = a.cmin;
-  const int nch = nblk > 0 ? (nblk + per - 1) / per : 0;
+  int per = nblk;  // blocks per chunk
+  if (a.nc > 1) per = max((int)(((unsigned)nblk + a.nc - 1) / (unsigned)a.nc), a.cmin);
 
   // Destination of this workgroup's result.
   const int64_t row0 = ((int64_t)(a.nc == 1 ? 0 : c) * a.B + b) * a.out_hq + hq0 - a.out_h0;
   float* __restrict__ out_dst = a.out + row0 * kHeadDim;
   float* __restrict__ lse_dst = a.lse + row0;
 
-  if (c >= nch) {  // empty range or chunk: out = 0, lse = -inf (chunk slots only need the lse)
+  if (nblk == 0 || (int64_t)c * per >= nblk) {  // empty range or chunk: out = 0, lse = -inf (chunk slots only need the lse)
     if (a.nc == 1) {
       for (int i = threadIdx.x; i < G * (kHeadDim / 4); i += 64 * W)
         reinterpret_cast<f32x4*>(out_dst)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -427,7 +431,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     return;
   }
   const int jb0 = c * per;
-  const int jb1 = min(nblk, jb0 + per);
+  const int jb1 = per < nblk - jb0 ? jb0 + per : nblk;
 
   bf16x8 qop[4];
   load_q(qop, a.q, (int64_t)b * a.Hq + hq0, col, quad, G);

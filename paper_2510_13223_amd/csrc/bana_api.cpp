@@ -375,6 +375,9 @@ bana_status run_attention(const bana_dims* d, const void* q, const void* k_cache
   a.nc = plan.nc;
   a.cmin = plan.cmin;
   a.seq_major = plan.seq_major;
+  a.by_ng.set((uint32_t)ng);
+  a.by_nc.set((uint32_t)plan.nc);
+  a.by_B.set((uint32_t)d->batch);
   // Workspace partials hold the call's heads only; merged rows go to their place in out / lse.
   a.out_hq = ng * G;
   a.out_h0 = g0 * G;

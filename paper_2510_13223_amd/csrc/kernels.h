@@ -41,6 +41,25 @@ struct SideCopies {
   int64_t n16[kMaxSideCopies];  // 16-byte units of each copy
 };
 
+// Division of a workgroup index (below 2^31) by a launch constant: a multiplication and a shift
+// of scalar registers instead of the GPU's some 30 instructions, at the start of every wavefront.
+struct FastDiv {
+  uint32_t mul = 1u << 31;
+  uint32_t shift = 31;
+
+  // 1 <= d < 2^31.  With 2^(shift - 31) >= d, mul = ceil(2^shift / d) exceeds 2^shift / d by less than
+  // 1, so n * mul / 2^shift exceeds n / d by less than n / 2^shift <= 1 / d for n < 2^31: the same floor.
+  void set(uint32_t d) {
+    shift = 31;
+    while ((1u << (shift - 31)) < d) ++shift;
+    mul = (uint32_t)(((uint64_t{1} << shift) + d - 1) / d);
+  }
+#ifdef __HIP__
+  __host__ __device__
+#endif
+  uint32_t quotient(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
+};
+
 struct PartialArgs {
   const uint16_t* q;        // bf16 [B][Hq][128]
   const uint16_t* k;        // bf16 [num_blocks][Hkv][128/8][16][8]
@@ -56,6 +75,7 @@ struct PartialArgs {
   int g0, ng;  // kv heads [g0, g0 + ng) of this launch
   int nc;    // chunks per (sequence, kv head)
   int cmin;  // minimum blocks per chunk
+  FastDiv by_ng, by_nc, by_B;
   bool seq_major;  // workgroup order: (sequence, chunk, kv head) instead of (chunk, sequence, kv head)
   // Destination rows: query head h of sequence b (chunk or piece slot c) goes to row
   // (c * B + b) * out_hq + h - out_h0 of out / lse.  Final output: out_hq = Hq, out_h0 = 0;

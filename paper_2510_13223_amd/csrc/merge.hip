@@ -34,6 +34,23 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// Rows of merged row r (below 2^26: a launch counts 32 threads each in 32 bits) in a part and in the
+// result.  Where all heads are merged, both are r; a kv-head range's rows take a division.
+struct Rows {
+  int64_t in, out;
+
+  static __device__ __forceinline__ unsigned sequence(const MergeRows& mr, unsigned r) { return r / (unsigned)mr.hn; }
+  __device__ __forceinline__ Rows(const MergeRows& mr, unsigned r) {
+    if (mr.hn == mr.in_hq && mr.hn == mr.out_hq) {
+      in = out = r;
+    } else {
+      const unsigned b = sequence(mr, r), i = r - b * mr.hn;
+      in = (int64_t)b * mr.in_hq + mr.in_h0 + i;
+      out = (int64_t)b * mr.out_hq + mr.out_h0 + i;
+    }
+  }
+};
+
 // At most NP parts, all loaded before use.  Parts with lse = -inf are loaded
 // too (their rows lie inside the partial buffer) but never enter a sum.
 template <int NP>
@@ -45,9 +62,8 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const float* __restrict_
   const int64_t r = (int64_t)blockIdx.x * 8 + (t >> 5);
   if (r >= mr.B * mr.hn) return;
   const int64_t rows = mr.B * mr.in_hq;
-  const int64_t b = r / mr.hn, i = r % mr.hn;
-  const int64_t row = b * mr.in_hq + mr.in_h0 + i;
-  const int64_t orow = b * mr.out_hq + mr.out_h0 + i;
+  const Rows at(mr, (unsigned)r);
+  const int64_t row = at.in, orow = at.out;
   float l[NP];
   f32x4 o[NP];
 #pragma unroll
@@ -111,23 +127,23 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const float* __restrict
   const int rl = t / (32 * KP);
   const int64_t r = (int64_t)blockIdx.x * R + rl;  // row among the B x hn merged rows
   const bool live = r < mr.B * mr.hn;
-  const int64_t b = live ? r / mr.hn : 0;
-  const int64_t i = live ? r % mr.hn : 0;
-  const int64_t dst_row = b * mr.out_hq + mr.out_h0 + i;
-  int64_t base = b * mr.in_hq + mr.in_h0 + i;
+  const Rows at(mr, live ? (unsigned)r : 0u);
+  const int64_t dst_row = at.out;
+  int64_t base = at.in;
   int64_t prow = mr.B * mr.in_hq;
   int n = n_parts;
   if (PIECES) {
     n = 0;
     prow = mr.in_hq;
     if (live) {
+      const unsigned b = at.sequence(mr, (unsigned)r), i = (unsigned)r - b * mr.hn;
       const int p0 = prefix[b], p1 = prefix[b + 1], total = prefix[mr.B];
-      const int64_t S = total > K ? ((int64_t)total + K - 1) / K : 1;
+      const unsigned S = total > K ? ((unsigned)total + K - 1) / (unsigned)K : 1u;
       if (p1 > p0) {  // slots clamped to [b, K + b): prefix sums from another call cannot reach outside
-        const int64_t first = min(max((int64_t)p0 / S, (int64_t)0), (int64_t)K - 1);
-        const int64_t last = min(max((int64_t)(p1 - 1) / S, first), (int64_t)K - 1);
+        const unsigned first = min((unsigned)p0 / S, (unsigned)K - 1);
+        const unsigned last = min(max((unsigned)(p1 - 1) / S, first), (unsigned)K - 1);
         n = (int)(last - first + 1);
-        base = (first + b) * mr.in_hq + mr.in_h0 + i;
+        base = (int64_t)(first + b) * mr.in_hq + mr.in_h0 + i;
       }
     }
   }
