@@ -251,6 +251,16 @@ struct Segments {
 
   __device__ __forceinline__ void load(const PartialArgs& a, int b, int lane, int n_parts) {
     t0 = t1 = jfirst = nblk = 0;
+    if (n_parts == 1) {  // one range, the same in every lane: scalar loads, nothing to sum
+      t0 = table_lookup(a.begin, 0, 0, b);
+      t1 = table_lookup(a.end, 0, 0, b);
+      if (t1 > t0) {
+        jfirst = t0 >> 4;
+        nblk = ((t1 - 1) >> 4) - jfirst + 1;
+      }
+      vend = nblk;
+      return;
+    }
     if (lane < n_parts) {
       t0 = a.begin[(int64_t)lane * a.B + b];
       t1 = a.end[(int64_t)lane * a.B + b];
@@ -260,7 +270,6 @@ struct Segments {
       }
     }
     vend = nblk;
-    if (n_parts == 1) return;  // one range: lane 0 holds it, nothing to sum
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const int y = __shfl_up(vend, off);

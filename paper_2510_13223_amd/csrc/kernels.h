@@ -103,7 +103,7 @@ struct MergeRows {
   int hn, in_hq, in_h0, out_hq, out_h0;
 };
 
-// Merge of the balanced launch's pieces (slots [K + B][in_hq]) into out / lse_out; kp (1, 2, 4 or 8)
+// Merge of the balanced launch's pieces (slots [K + B][in_hq]) into out / lse_out; kp (1, 2 or 8)
 // thread groups per merged row share its pieces.
 hipError_t launch_merge_pieces(const float* outs, const float* lses, const int32_t* prefix, int K, int kp,
                                MergeRows m, float* out, float* lse_out, hipStream_t stream);

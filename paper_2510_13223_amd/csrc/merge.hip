@@ -9,18 +9,20 @@
 // gives out = 0, lse_out = -inf.
 //
 // HBM-bound.  32 consecutive threads cover one 128-float row (16 bytes each,
-// one coalesced 512-byte access per part).  Two kernels:
+// one coalesced 512-byte access per part).  Three kernels:
 //  * up to four parts (the usual local + migrated split): every lse and every
 //    partial row is loaded up front, before any of them is used, so the
 //    kernel waits on one round of memory latency;
-//  * more parts (many migrated partitions, or the chunk partials of long
-//    ranges): the 32 lanes of a row first read 32 parts' lse at once and
-//    reduce their max with lane shuffles, then stream the partial rows with
-//    loads that do not depend on any lse (the weights come from the lanes by
-//    shuffle), so loads of consecutive parts overlap.  With few rows the parts
-//    of a row are spread over KP thread groups; each group keeps its sums
-//    relative to its own max and the KP groups are combined through LDS,
-//    rescaled to the common max (the same log-sum-exp algebra once more).
+//  * more parts of few rows (the chunks of few sequences): a row's parts spread
+//    over enough thread groups that each group takes them in one such round;
+//  * more parts of many rows, and the balanced launch's pieces: the 32 lanes of
+//    a row first read 32 parts' lse at once and reduce their max with lane
+//    shuffles, then stream the partial rows with loads that do not depend on
+//    any lse (the weights come from the lanes by shuffle), so loads of
+//    consecutive parts overlap.
+// Where a row has KP thread groups, each keeps its sums relative to its own max
+// and the groups are combined through LDS, rescaled to the common max (the same
+// log-sum-exp algebra once more).
 // The part-to-group assignment and every summation order depend only on
 // n_parts and the number of merged rows, so results are deterministic.
 #include <hip/hip_runtime.h>
@@ -47,6 +49,30 @@ struct Rows {
       const unsigned b = sequence(mr, r), i = r - b * mr.hn;
       in = (int64_t)b * mr.in_hq + mr.in_h0 + i;
       out = (int64_t)b * mr.out_hq + mr.out_h0 + i;
+    }
+  }
+};
+
+// The parts of a merged row: part p is row first + p * stride of the part buffers, p < n.  Partials
+// [n_parts][B][in_hq]: n_parts rows B x in_hq apart.  Pieces of the balanced launch: the pieces of a
+// sequence are consecutive slots of in_hq rows, counted from the block-count prefix sums (pieces =
+// intervals of S blocks that overlap the sequence's blocks [prefix[b], prefix[b + 1])).
+struct Parts {
+  int n;
+  int64_t first, stride;
+
+  __device__ __forceinline__ Parts(const MergeRows& mr, const Rows& at, int n_parts)
+      : n(n_parts), first(at.in), stride(mr.B * mr.in_hq) {}
+  __device__ __forceinline__ Parts(const MergeRows& mr, unsigned r, const int32_t* __restrict__ prefix, int K)
+      : n(0), first(0), stride(mr.in_hq) {
+    const unsigned b = Rows::sequence(mr, r), i = r - b * mr.hn;
+    const int p0 = prefix[b], p1 = prefix[b + 1], total = prefix[mr.B];
+    const unsigned S = total > K ? ((unsigned)total + K - 1) / (unsigned)K : 1u;
+    if (p1 > p0) {  // slots clamped to [b, K + b): prefix sums from another call cannot reach outside
+      const unsigned p = min((unsigned)p0 / S, (unsigned)K - 1);
+      const unsigned last = min(max((unsigned)(p1 - 1) / S, p), (unsigned)K - 1);
+      n = (int)(last - p + 1);
+      first = (int64_t)(p + b) * mr.in_hq + mr.in_h0 + i;
     }
   }
 };
@@ -97,14 +123,8 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const float* __restrict_
   if (lse_out != nullptr && d4 == 0) lse_out[orow] = M + logf(wsum);
 }
 
-// Any number of parts.  Group k (of KP) of a row takes parts k, k + KP, ...;
-// its q-th part is p = k + KP q.  Part p of merged row r (head i of sequence
-// b) is row base + p * prow of the part buffers: base = b * in_hq + in_h0 + i
-// and prow = B x in_hq for partials [n_parts][B][in_hq]; for the balanced
-// launch's pieces, base is the head's row in the sequence's first piece slot
-// and prow = in_hq (the slots of a sequence's pieces are consecutive), and the
-// part count comes from the block-count prefix sums (pieces = intervals of S
-// blocks that overlap the sequence's blocks [prefix[b], prefix[b + 1])).
+// Any number of parts of many rows.  Group k (of KP) of a row takes parts k, k + KP, ...;
+// its q-th part is p = k + KP q.
 //
 // Rows stream in rounds of U parts, each round requested before the previous one is summed (the
 // waits the compiler places keep about one round in flight per lane, its loads overlapping the
@@ -129,24 +149,10 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const float* __restrict
   const bool live = r < mr.B * mr.hn;
   const Rows at(mr, live ? (unsigned)r : 0u);
   const int64_t dst_row = at.out;
-  int64_t base = at.in;
-  int64_t prow = mr.B * mr.in_hq;
-  int n = n_parts;
-  if (PIECES) {
-    n = 0;
-    prow = mr.in_hq;
-    if (live) {
-      const unsigned b = at.sequence(mr, (unsigned)r), i = (unsigned)r - b * mr.hn;
-      const int p0 = prefix[b], p1 = prefix[b + 1], total = prefix[mr.B];
-      const unsigned S = total > K ? ((unsigned)total + K - 1) / (unsigned)K : 1u;
-      if (p1 > p0) {  // slots clamped to [b, K + b): prefix sums from another call cannot reach outside
-        const unsigned first = min((unsigned)p0 / S, (unsigned)K - 1);
-        const unsigned last = min(max((unsigned)(p1 - 1) / S, first), (unsigned)K - 1);
-        n = (int)(last - first + 1);
-        base = (int64_t)(first + b) * mr.in_hq + mr.in_h0 + i;
-      }
-    }
-  }
+  Parts parts(mr, at, live ? n_parts : 0);
+  if (PIECES && live) parts = Parts(mr, (unsigned)r, prefix, K);
+  const int n = parts.n;
+  const int64_t base = parts.first, prow = parts.stride;
   const int nq = live && n > k ? (n - k + KP - 1) / KP : 0;
   const int64_t lstride = (int64_t)KP * prow;                   // from the q-th part of the group to the next
   const float* lrow = lses + (int64_t)k * prow + base;           // lse of the q-th part: lrow[q * lstride]
@@ -236,6 +242,105 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const float* __restrict
   if (lse_out != nullptr && d4 == 0) lse_out[dst_row] = M + logf(wsum);
 }
 
+// Few rows of more than four parts (the chunks of few sequences, few partitions of a small batch): a
+// workgroup per row, its parts spread over KP thread groups, U per group and round.  Each thread
+// reads the lse of its parts itself, beside the rows (32 threads one word), so the group waits on one
+// round of memory latency and no shuffle: 32 rows of 32 parts 4.1 -> 3.5 us, 256 rows of 8 parts
+// 3.5 -> 3.0 us per call on MI355X (HIP graph).  Later rounds rescale to the running max.
+template <int KP, int U>
+__global__ __launch_bounds__(32 * KP) void merge_spread_kernel(const float* __restrict__ outs,
+                                                               const float* __restrict__ lses, int n_parts,
+                                                               MergeRows mr, float* __restrict__ out,
+                                                               float* __restrict__ lse_out) {
+  __shared__ f32x4 sm_acc[KP * 32];
+  __shared__ float sm_m[KP];
+  __shared__ float sm_w[KP];
+  const int d4 = threadIdx.x & 31;
+  const int k = threadIdx.x >> 5;
+  const Rows at(mr, blockIdx.x);
+  const Parts parts(mr, at, n_parts);
+  float m = -INFINITY, wsum = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float l[U];
+  f32x4 o[U];
+  auto request = [&](int p0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = p0 + u * KP;
+      l[u] = -INFINITY;
+      if (p < parts.n) {
+        const int64_t row = parts.first + p * parts.stride;
+        l[u] = lses[row];
+        o[u] = reinterpret_cast<const f32x4*>(outs + row * 128)[d4];
+      }
+    }
+  };
+  request(k);
+  for (int p0 = k; p0 < parts.n; p0 += KP * U) {
+    float lc[U];
+    f32x4 oc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      lc[u] = l[u];
+      oc[u] = o[u];
+    }
+    if (p0 + KP * U < parts.n) request(p0 + KP * U);  // the next round, before this one is summed
+    float top = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) top = fmaxf(top, lc[u]);
+    if (top == -INFINITY) continue;
+    const float scale = expf(m - top);
+    acc *= scale;
+    wsum *= scale;
+    m = top;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (lc[u] != -INFINITY) {  // rows of empty parts never enter a sum
+        const float w = expf(lc[u] - top);
+        wsum += w;
+        acc += w * oc[u];
+      }
+    }
+  }
+  race_check_delay(threadIdx.x >> 6);
+  sm_acc[k * 32 + d4] = acc;
+  if (d4 == 0) {
+    sm_m[k] = m;
+    sm_w[k] = wsum;
+  }
+  __syncthreads();
+  race_check_barrier();
+  if (k != 0) return;
+  float M = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < KP; ++j) M = fmaxf(M, sm_m[j]);
+  f32x4* dst = reinterpret_cast<f32x4*>(out + at.out * 128) + d4;
+  if (M == -INFINITY) {
+    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (lse_out != nullptr && d4 == 0) lse_out[at.out] = -INFINITY;
+    return;
+  }
+  acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  wsum = 0.f;
+#pragma unroll
+  for (int j = 0; j < KP; ++j) {
+    if (sm_m[j] == -INFINITY) continue;
+    const float s = expf(sm_m[j] - M);
+    acc += s * sm_acc[j * 32 + d4];
+    wsum += s * sm_w[j];
+  }
+  *dst = acc * (1.0f / wsum);
+  if (lse_out != nullptr && d4 == 0) lse_out[at.out] = M + logf(wsum);
+}
+
+template <int KP>
+hipError_t launch_spread(const float* outs, const float* lses, int n_parts, const MergeRows& m, float* out,
+                         float* lse_out, hipStream_t stream) {
+  hipLaunchKernelGGL((merge_spread_kernel<KP, 4>), dim3((unsigned)(m.B * m.hn)), dim3(32 * KP), 0, stream, outs, lses,
+                     n_parts, m, out, lse_out);
+  return hipGetLastError();
+}
+
 template <int KP, bool PIECES = false>
 hipError_t launch_many(const float* outs, const float* lses, int n_parts, const MergeRows& m, float* out,
                        float* lse_out, hipStream_t stream, const int32_t* prefix = nullptr, int K = 0) {
@@ -261,12 +366,15 @@ hipError_t launch_merge(const float* outs, const float* lses, int n_parts, Merge
   }
   // With enough rows to fill the GPU, one thread group per row streams best.
   // With few rows (the chunks of few sequences, few partitions), spread a row's
-  // parts over 4 or 8 thread groups: a group then takes its parts in one round of
-  // loads or few.  One group per row took its parts one after the other (256 rows of
-  // 7 parts after a 50-block range's chunks: the call 10.0 us against 8.8).
-  if (rows < 4096) {
-    if (n_parts >= 17) return launch_many<8>(outs, lses, n_parts, m, out, lse_out, stream);
-    return launch_many<4>(outs, lses, n_parts, m, out, lse_out, stream);
+  // parts over enough thread groups that each takes them in one round of loads.
+  // More rows stream better with one group each, the more parts the sooner (us per call, spread /
+  // one group: 8,192 rows of 5, 8, 16, 40 parts 6.9 / 6.9, 8.5 / 9.2, 13.5 / 15.2, 39.6 / 32.9; 16,384
+  // rows of 5, 16 parts 10.7 / 9.7, 30.9 / 24.6).
+  if (rows < 4096 || (rows <= 8192 && n_parts >= 8 && n_parts <= 16)) {
+    if (n_parts <= 8) return launch_spread<2>(outs, lses, n_parts, m, out, lse_out, stream);
+    if (n_parts <= 16) return launch_spread<4>(outs, lses, n_parts, m, out, lse_out, stream);
+    if (n_parts <= 32) return launch_spread<8>(outs, lses, n_parts, m, out, lse_out, stream);
+    return launch_spread<16>(outs, lses, n_parts, m, out, lse_out, stream);
   }
   return launch_many<1>(outs, lses, n_parts, m, out, lse_out, stream);
 }
@@ -278,7 +386,6 @@ hipError_t launch_merge_pieces(const float* outs, const float* lses, const int32
   switch (kp) {
     case 1: return launch_many<1, true>(outs, lses, 0, m, out, lse_out, stream, prefix, K);
     case 2: return launch_many<2, true>(outs, lses, 0, m, out, lse_out, stream, prefix, K);
-    case 4: return launch_many<4, true>(outs, lses, 0, m, out, lse_out, stream, prefix, K);
     case 8: return launch_many<8, true>(outs, lses, 0, m, out, lse_out, stream, prefix, K);
     default: return hipErrorInvalidValue;
   }
