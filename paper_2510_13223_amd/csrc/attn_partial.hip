@@ -229,15 +229,20 @@ struct Online {
     }
   }
 
-  // Normalised rows of the G heads (out_dst row = head in group) and their lse.
+  // Normalised rows of the G heads (out_dst row = head in group) and their lse.  STREAM: rows that no
+  // kernel reads soon, stored past the caches.
+  template <bool STREAM>
   __device__ __forceinline__ void emit(float* __restrict__ out_dst, float* __restrict__ lse_dst, int col, int quad,
                                        int G) {
     const float l = column_sum(lsum);
     if (col < G) {
       const float inv = 1.0f / l;
 #pragma unroll
-      for (int dt = 0; dt < kDimTiles; ++dt)
-        *reinterpret_cast<f32x4*>(out_dst + col * kHeadDim + 16 * dt + 4 * quad) = acc[dt] * inv;
+      for (int dt = 0; dt < kDimTiles; ++dt) {
+        f32x4* dst = reinterpret_cast<f32x4*>(out_dst + col * kHeadDim + 16 * dt + 4 * quad);
+        if (STREAM) __builtin_nontemporal_store(acc[dt] * inv, dst);
+        else *dst = acc[dt] * inv;
+      }
       if (quad == 0) lse_dst[col] = m + logf(l);
     }
   }
@@ -449,7 +454,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
   walk_blocks<W>(st, qop, sg, n_parts, a, b, g, col, quad, jb0 + wave, jb1);
 
   if (W == 1) {
-    st.emit(out_dst, lse_dst, col, quad, G);
+    // One wavefront per pair: thousands of pairs, whose rows (8 MB and more) would be dirty in the L2s
+    // at the end of the launch, which waits for them to be written back.  Stored past the caches they
+    // are gone by then: fine's 16 calls (16.9 MB of rows each) and merge 840 -> 824 us on MI355X.  The
+    // rows of split and balanced launches are read by the next kernel, which that makes slower (a
+    // balanced call of 79 us by 6), and so are those of wider workgroups (2 x 1 MB of rows: 1 us).
+    if (a.nc == 1) st.emit<true>(out_dst, lse_dst, col, quad, G);
+    else st.emit<false>(out_dst, lse_dst, col, quad, G);
     BANA_TIMELINE_MARK(3);
     return;
   }
@@ -594,7 +605,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     st.init();
     walk_blocks<1>(st, qop, sg, a.n_parts, a, b, g, col, quad, v0, v1);
     const int64_t row0 = (int64_t)(k + b) * a.out_hq + hq0 - a.out_h0;
-    st.emit(a.out + row0 * kHeadDim, a.lse + row0, col, quad, G);
+    st.emit<false>(a.out + row0 * kHeadDim, a.lse + row0, col, quad, G);
     pos = pb + v1;
   }
   BANA_TIMELINE_MARK(3);

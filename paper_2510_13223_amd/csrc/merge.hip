@@ -238,7 +238,10 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const float* __restrict
     if (lse_out != nullptr && d4 == 0) lse_out[dst_row] = -INFINITY;
     return;
   }
-  *dst = acc * (1.0f / wsum);
+  // Many rows: stored past the caches, so that the launch does not end with them dirty in the L2s
+  // (fine's 32,768 rows, 16.8 MB: 2 us of 48).
+  if (KP == 1 && !PIECES) __builtin_nontemporal_store(acc * (1.0f / wsum), dst);
+  else *dst = acc * (1.0f / wsum);
   if (lse_out != nullptr && d4 == 0) lse_out[dst_row] = M + logf(wsum);
 }
 
