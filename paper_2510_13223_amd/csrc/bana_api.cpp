@@ -37,11 +37,12 @@ constexpr int kFewUnevenGroups = 768;  // where the longest is less than twice t
 constexpr int kFewLongGroups = 1024;   // four times the mean, six beyond
 constexpr int kFewRaggedGroups = 1536;
 constexpr int kMinChunkBlocks = 4;     // of the longest range's chunks
-constexpr int kMinUnevenBlocks = 24;   // (block, kv head) units per workgroup on the mean: less than
+constexpr int kMinUnevenBlocks = 12;   // (block, kv head) units per workgroup on the mean: less than
 constexpr int kMinLongBlocks = 5;      // twice the mean, beyond
 constexpr int kLongChunkBlocks = 48;   // uneven chunks from here on get 8 wavefronts
-constexpr int kUnsplitBlocks = 32;     // ranges of at most this many blocks are not cut
-constexpr int kBalancedSaves = 4;
+constexpr int kUnsplitBlocks = 28;     // ranges of at most this many blocks are not cut,
+constexpr int kShortBlocks = 64;       // and of at most this many (twice without hints) not always
+constexpr int kBalancedSaves = 8;
 constexpr int kBalancedLongWalk = 40;
 constexpr int64_t kSlotBytes = (kHeadDim + 1) * sizeof(float);  // a partial row and its lse
 constexpr int64_t kScratchForSplits = (int64_t)bana::kStaticScratchBytes - 4096;
@@ -145,7 +146,8 @@ int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // chunked against 214 / 263 us balanced; its 1024-pair head halves 317
 // against 278 us; long's fused call, 1.3 x spread, 494 against 478 us).
 // kBalancedSaves: log-normal lengths, blocks saved and us chunked / balanced:
-// -6 49 / 54, -2 92 / 95, 1 91 / 86, 3 107 / 103, 14 125 / 107.
+// -6 49 / 54, -2 92 / 95, 1 91 / 86, 3 107 / 103, 14 125 / 107; in shorter calls its merge
+// weighs more: 4 21 / 28.
 //
 // split: whether the call has workspace for the plan.  Without it every range
 // stays in one workgroup, which then wants as many wavefronts as it can use.
@@ -222,6 +224,7 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   }
   const bool few = d->waves_hint == 0 && d->chunks_hint == 0 && active_pairs < (hinted ? kFewPairs : kFewPairs / 2);
   int64_t few_chunks = 1;
+  bool uncut = !split;  // one workgroup per range, whatever its length
   if (few && split && bound > kUnsplitBlocks) {
     few_chunks = std::min<int64_t>(few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks));
     // Without hints no wavefront walks more than kMaxBlocksPerWave blocks.
@@ -229,13 +232,23 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     // Few active sequences of a large batch: keep the chunk partials of all of it small.
     few_chunks = std::min<int64_t>(few_chunks, kScratchForSplits / ((int64_t)d->batch * d->num_q_heads * kSlotBytes));
     few_chunks = std::max<int64_t>(few_chunks, 1);
+    // Short ranges are cut only where that spares a wavefront enough blocks to pay for the merge
+    // launch, against one workgroup of as many wavefronts as the LDS combine allows: 2 blocks, or 8
+    // without hints, where the ranges may be much shorter than the table is wide (16 sequences of 800
+    // tokens, 8 heads: 13.3 us, cut in two 13.9; 51 of 635 in 4 partitions, no hints: 46 us, cut 50).
+    const int most_waves = d->num_q_heads / d->num_kv_heads == kMaxGroup ? 4 : 8;
+    if (bound <= (hinted ? kShortBlocks : 2 * kShortBlocks) &&
+        bound / most_waves - bound / (4 * few_chunks) < (hinted ? 2 : 8)) {
+      few_chunks = 1;
+      uncut = true;
+    }
   }
   if (d->waves_hint > 0)
     p.waves = d->waves_hint;
   else if (few && bound <= kUnsplitBlocks)
-    p.waves = bound <= kUnsplitBlocks / 2 ? 4 : 8;
+    p.waves = bound <= 16 ? 4 : 8;
   else if (few)
-    p.waves = !split || (uneven && bound >= kLongChunkBlocks * few_chunks) ? 8 : 4;
+    p.waves = uncut || (uneven && bound >= kLongChunkBlocks * few_chunks) ? 8 : 4;
   else if (uneven && bound >= 8 * kMinBlocksPerWave)
     p.waves = 8;
   else

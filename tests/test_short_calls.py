@@ -21,10 +21,14 @@ def _chunks(B, Hq, Hkv, longest, total, **kw):
     return max(1, round(ws / (B * Hq * ROW_BYTES))), ws
 
 
-def test_ranges_of_up_to_32_blocks_are_not_cut():
+def test_short_ranges_are_not_cut():
     for B, Hkv in ((1, 1), (1, 8), (8, 2), (31, 8)):
-        assert _chunks(B, 4 * Hkv, Hkv, 512, 512 * B) == (1, 0)
-        assert _chunks(B, 4 * Hkv, Hkv, 528, 528 * B)[0] == (9 if B * Hkv <= 16 else 1)
+        assert _chunks(B, 4 * Hkv, Hkv, 448, 448 * B) == (1, 0)
+        assert _chunks(B, 4 * Hkv, Hkv, 464, 464 * B)[0] == (8 if B * Hkv <= 16 else 1)
+    # up to 64 blocks (128 without hints) only where that spares a wavefront enough of them
+    assert _chunks(16, 32, 8, 800, 16 * 800)[0] == 1
+    assert _chunks(8, 32, 8, 800, 8 * 800)[0] == 4
+    assert _chunks(51, 28, 4, 1024, 0) == (1, 0) and _chunks(1, 32, 8, 2048, 0)[0] > 1
 
 
 def test_even_ranges_get_one_workgroup_per_cu():
@@ -50,8 +54,8 @@ GPU_CASES = [
     # B, Hq, Hkv, lengths (cycled), parts
     (1, 4, 1, [256], 1),          # a whole range per workgroup: 16 blocks, 4 wavefronts
     (1, 16, 1, [257], 1),         # 17 blocks, 8 wavefronts
-    (3, 8, 2, [512, 511, 500], 1),
-    (3, 8, 2, [513, 514, 528], 2),  # 33 blocks: cut, one block per wavefront
+    (3, 8, 2, [448, 447, 440], 1),
+    (3, 8, 2, [449, 450, 464], 2),  # 29 blocks: cut, one block per wavefront
     (1, 2, 2, [5000], 2),         # 128 chunks allowed, 79 used
     (17, 32, 16, [700], 1),       # 272 pairs: one chunk
     (16, 32, 16, [700, 690], 1),  # 256 pairs
