@@ -291,8 +291,9 @@ __global__ __launch_bounds__(32 * KP) void merge_spread_kernel(const float* __re
     float top = m;
 #pragma unroll
     for (int u = 0; u < U; ++u) top = fmaxf(top, lc[u]);
-    if (top == -INFINITY) continue;
-    const float scale = expf(m - top);
+    // A NaN lse is not in the max but must reach the result, also from a group or round whose other
+    // parts are empty: its weight is NaN below, and no sum is left out on account of a max of -inf.
+    const float scale = m == top ? 1.f : expf(m - top);
     acc *= scale;
     wsum *= scale;
     m = top;
@@ -327,8 +328,7 @@ __global__ __launch_bounds__(32 * KP) void merge_spread_kernel(const float* __re
   wsum = 0.f;
 #pragma unroll
   for (int j = 0; j < KP; ++j) {
-    if (sm_m[j] == -INFINITY) continue;
-    const float s = expf(sm_m[j] - M);
+    const float s = expf(sm_m[j] - M);  // 0 for a group of empty parts, whose sums are 0 (or NaN)
     acc += s * sm_acc[j * 32 + d4];
     wsum += s * sm_w[j];
   }

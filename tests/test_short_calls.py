@@ -85,3 +85,18 @@ def test_merge_of_few_rows_at_its_edges(n):
     from test_gpu_parity import test_merge_matches_oracle_merge
 
     test_merge_matches_oracle_merge(n, 3, 8)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [5, 8, 16, 17, 33, 96])
+def test_merge_of_few_rows_keeps_a_nan_lse(n):
+    """Row r: part r % n has a NaN lse, the next part a finite one, the others are empty."""
+    import torch
+
+    lses = torch.full((n, n, 4), -math.inf)
+    for b in range(n):
+        lses[b, b] = math.nan
+        lses[(b + 1) % n, b] = 1.0
+    out, lse = torch.zeros(n, 4, 128, device="cuda"), torch.zeros(n, 4, device="cuda")
+    bana.bana_merge_partials(torch.ones(n, n, 4, 128, device="cuda"), lses.cuda(), out, lse)
+    assert torch.isnan(out).all() and torch.isnan(lse).all()
