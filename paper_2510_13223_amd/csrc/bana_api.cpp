@@ -37,9 +37,13 @@ constexpr int kFewUnevenGroups = 768;  // where the longest is less than twice t
 constexpr int kFewLongGroups = 1024;   // four times the mean, six beyond
 constexpr int kFewRaggedGroups = 1536;
 constexpr int kMinChunkBlocks = 4;     // of the longest range's chunks
+constexpr int kMinUnknownBlocks = 16;  // of a chunk of 8 wavefronts without range hints
 constexpr int kMinUnevenBlocks = 12;   // (block, kv head) units per workgroup on the mean: less than
 constexpr int kMinLongBlocks = 5;      // twice the mean, beyond
 constexpr int kLongChunkBlocks = 48;   // uneven chunks from here on get 8 wavefronts
+constexpr int kUnknownChunkLow = 64;   // chunks without range hints: at most a sixth of the table's width,
+constexpr int kUnknownChunkHigh = 192; // not below the one nor above the other
+constexpr int kUnknownChunkHigh4 = 256; // (the other where the LDS combine allows 4 wavefronts only)
 constexpr int kUnsplitBlocks = 28;     // ranges of at most this many blocks are not cut,
 constexpr int kShortBlocks = 64;       // and of at most this many (twice without hints) not always
 constexpr int kBalancedSaves = 8;
@@ -126,6 +130,12 @@ int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 //                          48 sequences of 800                     33 -> 28
 //   64 / 8                 12 log-normal around 6000 (balanced)    71.5 -> 66
 //   28 / 4                 16 log-normal around 6000 (balanced)    54.5 -> 49
+// Without hints the longest range may hold most of the blocks, so chunks stay below kUnknownChunkHigh
+// blocks (below a sixth of shorter tables), of 8 wavefronts.  Fused calls without hints, us: chunks of up
+// to 512 blocks and 4 wavefronts -> this rule -> chunks half / twice as long:
+//   32 / 8, 23 log-normal, up to 2799 blocks  255 -> 226 -> 229 / 246    50, up to 2555  323 -> 267 -> 272 / 290
+//   32 / 8, 40 log-normal, up to 505 blocks   108 -> 63 -> 64 / 74       23 even of 483  130 -> 115 -> 123 / 117
+//   28 / 4, 60 log-normal, up to 1307 blocks  119 -> 101 -> 104 / 115    64 / 8, 8, up to 3063  135 -> 114 -> 123 / 126
 // (even ranges at two workgroups per CU: 3 % slower or more, at half a workgroup 4 to 20 %; from 1024
 // pairs on the rule for many pairs gives one chunk of as many wavefronts).
 //
@@ -227,8 +237,22 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   bool uncut = !split;  // one workgroup per range, whatever its length
   if (few && split && bound > kUnsplitBlocks) {
     few_chunks = std::min<int64_t>(few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks));
-    // Without hints no wavefront walks more than kMaxBlocksPerWave blocks.
-    if (!hinted) few_chunks = std::max<int64_t>(few_chunks, ceil_div(bound, 8 * kMaxBlocksPerWave));
+    // Without hints the ranges may be uneven: chunks of a sixth of the table's width, within bounds.
+    if (!hinted) {
+      const int64_t high = d->num_q_heads / d->num_kv_heads == kMaxGroup ? kUnknownChunkHigh4 : kUnknownChunkHigh;
+      const int64_t most = std::max<int64_t>(kUnknownChunkLow, std::min<int64_t>(bound / 6, high));
+      const int64_t least = ceil_div(bound, most);
+      // Up to half as many more where that fills the last round of one workgroup per CU: even ranges
+      // all end together (56 pairs of 1875 blocks in 8, 9, 10 chunks: 140, 142, 160 us).
+      if (least > few_chunks) {
+        auto fill = [&](int64_t n) {
+          return (double)(n * active_pairs) / (kFewEvenGroups * ceil_div(n * active_pairs, kFewEvenGroups));
+        };
+        few_chunks = least;
+        for (int64_t n = least + 1; 2 * n <= 3 * least; ++n)
+          if (fill(n) > fill(few_chunks) + 0.02) few_chunks = n;
+      }
+    }
     // Few active sequences of a large batch: keep the chunk partials of all of it small.
     few_chunks = std::min<int64_t>(few_chunks, kScratchForSplits / ((int64_t)d->batch * d->num_q_heads * kSlotBytes));
     few_chunks = std::max<int64_t>(few_chunks, 1);
@@ -248,7 +272,7 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   else if (few && bound <= kUnsplitBlocks)
     p.waves = bound <= 16 ? 4 : 8;
   else if (few)
-    p.waves = uncut || (uneven && bound >= kLongChunkBlocks * few_chunks) ? 8 : 4;
+    p.waves = uncut || ((uneven || !hinted) && bound >= kLongChunkBlocks * few_chunks) ? 8 : 4;
   else if (uneven && bound >= 8 * kMinBlocksPerWave)
     p.waves = 8;
   else
@@ -262,7 +286,7 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     p.cmin = 1;
   } else if (few) {
     p.nc = (int)few_chunks;
-    p.cmin = 1;
+    p.cmin = !hinted && p.waves == 8 ? kMinUnknownBlocks : 1;  // a range may be far below the table's width
     p.seq_major = true;
   } else if (hinted) {
     // (block, kv head) units of the call and the blocks per wavefront if they

@@ -31,6 +31,12 @@ def test_short_ranges_are_not_cut():
     assert _chunks(51, 28, 4, 1024, 0) == (1, 0) and _chunks(1, 32, 8, 2048, 0)[0] > 1
 
 
+def test_without_hints_chunks_stay_below_a_bound():
+    for B, G, Hkv, blocks, want in ((40, 4, 8, 505, 8), (23, 4, 8, 2799, 15), (60, 4, 8, 129, 3), (63, 4, 8, 384, 6),
+                                    (1, 4, 8, 3750, 64), (28, 16, 2, 1875, 9), (28, 16, 2, 8192, 32)):
+        assert _chunks(B, G * Hkv, Hkv, 16 * blocks, 0)[0] == want, (B, Hkv, blocks)
+
+
 def test_even_ranges_get_one_workgroup_per_cu():
     for B, Hkv in ((1, 2), (3, 8), (16, 8), (32, 8), (33, 8), (100, 8)):
         n, _ = _chunks(B, 4 * Hkv, Hkv, 100000, 100000 * B)
@@ -62,6 +68,8 @@ GPU_CASES = [
     (5, 8, 4, [4000, 2500, 2600, 2500, 2500], 2),   # longest below twice the mean
     (6, 32, 8, [6000, 900, 1200, 800, 1, 900], 1),  # up to four times
     (9, 16, 1, [9000, 300, 17, 40, 200, 600, 5, 90, 333], 3),  # beyond, group of 16
+    (65, 8, 4, [2064, 1, 255, 256, 257, 15], 1),  # 129 blocks wide: without hints 3 chunks, of 16 blocks at least
+    (65, 16, 1, [6200, 30, 1025, 1040], 2),       # likewise 388 blocks, group of 16
 ]
 
 
