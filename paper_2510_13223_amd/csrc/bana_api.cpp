@@ -37,7 +37,7 @@ constexpr int kFewUnevenGroups = 768;  // where the longest is less than twice t
 constexpr int kFewLongGroups = 1024;   // four times the mean, six beyond
 constexpr int kFewRaggedGroups = 1536;
 constexpr int kMinChunkBlocks = 4;     // of the longest range's chunks
-constexpr int kMinUnknownBlocks = 16;  // of a chunk of 8 wavefronts without range hints
+constexpr int kMinUnknownBlocks = 16;  // of a chunk without range hints, tables of some hundred blocks
 constexpr int kMinUnevenBlocks = 12;   // (block, kv head) units per workgroup on the mean: less than
 constexpr int kMinLongBlocks = 5;      // twice the mean, beyond
 constexpr int kLongChunkBlocks = 48;   // uneven chunks from here on get 8 wavefronts
@@ -234,6 +234,7 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   }
   const bool few = d->waves_hint == 0 && d->chunks_hint == 0 && active_pairs < (hinted ? kFewPairs : kFewPairs / 2);
   int64_t few_chunks = 1;
+  int min_chunk = 1;
   bool uncut = !split;  // one workgroup per range, whatever its length
   if (few && split && bound > kUnsplitBlocks) {
     few_chunks = std::min<int64_t>(few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks));
@@ -248,6 +249,10 @@ Plan make_plan(const bana_dims* d, bool split = true) {
         auto fill = [&](int64_t n) {
           return (double)(n * active_pairs) / (kFewEvenGroups * ceil_div(n * active_pairs, kFewEvenGroups));
         };
+        // Ranges far below the table's width stay in chunks of a third of that (28 log-normal ones of up to
+        // 12509 blocks, group of 16, two kv heads: 349 us at 1 block, 342 so; 50 of up to 2555: 270, 259; 40 of up to
+        // 505, at 16 and 28 blocks: 63, 66, so narrower tables keep 16).
+        min_chunk = most >= kUnknownChunkHigh ? (int)(most / 3) : kMinUnknownBlocks;
         few_chunks = least;
         for (int64_t n = least + 1; 2 * n <= 3 * least; ++n)
           if (fill(n) > fill(few_chunks) + 0.02) few_chunks = n;
@@ -286,7 +291,7 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     p.cmin = 1;
   } else if (few) {
     p.nc = (int)few_chunks;
-    p.cmin = !hinted && p.waves == 8 ? kMinUnknownBlocks : 1;  // a range may be far below the table's width
+    p.cmin = min_chunk;
     p.seq_major = true;
   } else if (hinted) {
     // (block, kv head) units of the call and the blocks per wavefront if they
