@@ -6,7 +6,9 @@
 //   M = max_p lse_p,  w_p = exp(lse_p - M),
 //   out = sum_p w_p out_p / sum_p w_p,  lse_out = M + ln sum_p w_p,
 // skipping parts with lse_p = -inf (their out_p never enters a sum); no live part
-// gives out = 0, lse_out = -inf.
+// gives out = 0, lse_out = -inf.  A NaN lse is not in M but has a NaN weight, so
+// a row is empty where its weights sum to 0 and not where M is -inf: a row with
+// parts whose lse is NaN, and no others, is NaN.
 //
 // HBM-bound.  32 consecutive threads cover one 128-float row (16 bytes each,
 // one coalesced 512-byte access per part).  Three kernels:
@@ -104,11 +106,6 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const float* __restrict_
   for (int p = 0; p < NP; ++p)
     if (p < n_parts) M = fmaxf(M, l[p]);
   f32x4* dst = reinterpret_cast<f32x4*>(out + orow * 128) + d4;
-  if (M == -INFINITY) {
-    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (lse_out != nullptr && d4 == 0) lse_out[orow] = -INFINITY;
-    return;
-  }
   float wsum = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -118,6 +115,11 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const float* __restrict_
       wsum += w;
       acc += w * o[p];
     }
+  }
+  if (wsum == 0.f) {
+    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (lse_out != nullptr && d4 == 0) lse_out[orow] = -INFINITY;
+    return;
   }
   *dst = acc * (1.0f / wsum);
   if (lse_out != nullptr && d4 == 0) lse_out[orow] = M + logf(wsum);
@@ -170,13 +172,18 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const float* __restrict
   for (int u = 0; u < U; ++u)
     if (u < nq) o[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(orow + u * lstride * 128) + d4);
   float m = l0;
-  for (int q = d4 + 32; q < nq; q += 32) m = fmaxf(m, lrow[q * lstride]);
+  bool full = l0 != -INFINITY;  // a NaN part is not empty
+  for (int q = d4 + 32; q < nq; q += 32) {
+    const float lq = lrow[q * lstride];
+    m = fmaxf(m, lq);
+    full |= lq != -INFINITY;
+  }
 #pragma unroll
   for (int off = 16; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 32));
 
   float wsum = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (m != -INFINITY) {
+  if ((uint32_t)(__ballot(full) >> (t & 32)) != 0) {  // any part of the group's 32 lanes
     // Weight of part 32r + d4 on lane d4 for the current round r of 32 parts (0 past the end
     // and for empty parts).
     float wq = l0 == -INFINITY ? 0.f : expf(l0 - m);
@@ -220,20 +227,17 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const float* __restrict
     for (int j = 0; j < KP; ++j) M = fmaxf(M, sm_m[rl * KP + j]);
     acc = f32x4{0.f, 0.f, 0.f, 0.f};
     wsum = 0.f;
-    if (M != -INFINITY) {
 #pragma unroll
-      for (int j = 0; j < KP; ++j) {
-        const float mj = sm_m[rl * KP + j];
-        if (mj == -INFINITY) continue;
-        const float s = expf(mj - M);
-        acc += s * sm_acc[(rl * KP + j) * 32 + d4];
-        wsum += s * sm_w[rl * KP + j];
-      }
+    for (int j = 0; j < KP; ++j) {
+      const float mj = sm_m[rl * KP + j];
+      const float s = mj == M ? 1.f : expf(mj - M);  // 0 for a group of empty parts, whose sums are 0 (or NaN)
+      acc += s * sm_acc[(rl * KP + j) * 32 + d4];
+      wsum += s * sm_w[rl * KP + j];
     }
   }
   if (!live) return;
   f32x4* dst = reinterpret_cast<f32x4*>(out + dst_row * 128) + d4;
-  if (M == -INFINITY) {
+  if (wsum == 0.f) {
     *dst = f32x4{0.f, 0.f, 0.f, 0.f};
     if (lse_out != nullptr && d4 == 0) lse_out[dst_row] = -INFINITY;
     return;
@@ -319,18 +323,18 @@ __global__ __launch_bounds__(32 * KP) void merge_spread_kernel(const float* __re
 #pragma unroll
   for (int j = 0; j < KP; ++j) M = fmaxf(M, sm_m[j]);
   f32x4* dst = reinterpret_cast<f32x4*>(out + at.out * 128) + d4;
-  if (M == -INFINITY) {
-    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (lse_out != nullptr && d4 == 0) lse_out[at.out] = -INFINITY;
-    return;
-  }
   acc = f32x4{0.f, 0.f, 0.f, 0.f};
   wsum = 0.f;
 #pragma unroll
   for (int j = 0; j < KP; ++j) {
-    const float s = expf(sm_m[j] - M);  // 0 for a group of empty parts, whose sums are 0 (or NaN)
+    const float s = sm_m[j] == M ? 1.f : expf(sm_m[j] - M);  // 0 for a group of empty parts, whose sums are 0 (or NaN)
     acc += s * sm_acc[j * 32 + d4];
     wsum += s * sm_w[j];
+  }
+  if (wsum == 0.f) {
+    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (lse_out != nullptr && d4 == 0) lse_out[at.out] = -INFINITY;
+    return;
   }
   *dst = acc * (1.0f / wsum);
   if (lse_out != nullptr && d4 == 0) lse_out[at.out] = M + logf(wsum);
