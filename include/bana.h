@@ -120,6 +120,7 @@ typedef struct {
  *   lse[b][h]         = m + ln sum_{t in T} exp(s_t - m),   m = max_{t in T} s_t
  * with s_t = q[b][h] . k_t.  An empty T gives out_partial = 0, lse = -inf.
  * Ranges need not be block aligned.  bf16 inputs, fp32 accumulation.
+ * A NaN among a row's scores makes the row and its lse NaN.
  *
  * workspace: optional device scratch of workspace_bytes bytes, at least
  * bana_decode_attn_workspace_bytes(d) for ranges to be split across several

@@ -205,7 +205,7 @@ struct Online {
     }
 
     const float mx = column_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
-    const float m_new = fmaxf(m, mx);  // finite: every visited block covers >= 1 token
+    const float m_new = fmaxf(m, mx);  // finite unless scores are not: every visited block covers >= 1 token
     const float alpha = fast_exp2((m - m_new) * kLog2e);
     float p[4];
 #pragma unroll
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
   float* sm_acc = smem + 32 * W;    // [W][G][kRowPad]
   race_check_delay(wave);
   if (quad == 0) {
-    sm_m[wave * 16 + col] = st.m;   // -inf for a wave that saw no block
+    sm_m[wave * 16 + col] = st.m;   // -inf for a wave that saw no block (or only NaN scores)
     sm_l[wave * 16 + col] = lsum;
   }
   if (col < G) {
@@ -489,10 +489,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     for (int w = 0; w < W; ++w) M = fmaxf(M, sm_m[w * 16 + h]);
     float L = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    // A wavefront without a block adds 0 x 0.  One whose scores were all NaN also has m = -inf, but NaN
+    // sums, which stay NaN under any weight (with no other wavefront the weight is NaN as well).
 #pragma unroll
     for (int w = 0; w < W; ++w) {
       const float mw = sm_m[w * 16 + h];
-      if (mw == -INFINITY) continue;
       const float e = fast_exp2((mw - M) * kLog2e);
       L += e * sm_l[w * 16 + h];
       o += e * *reinterpret_cast<const f32x4*>(sm_acc + (w * G + h) * kRowPad + 4 * d4);

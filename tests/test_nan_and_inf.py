@@ -49,3 +49,43 @@ def test_merge_of_rows_with_only_nan_and_empty_parts(n, B, Hq):
     bad = (kind >= 1) & (kind <= 3)
     assert torch.isnan(out[bad]).all() and torch.isnan(lse[bad]).all()
     assert (out[kind == 4] == 1).all() and (lse[kind == 4] == 2).all()
+
+
+# (hints, workspace): the library's choice, whole ranges on 1, 4 and 8 wavefronts, chunks of each, the balanced launch.
+PLANS = [{}, {"range_hints": False}, {"use_workspace": False}, {"plan_hint": 2},
+         *({"waves_hint": w, "chunks_hint": c} for w, c in ((1, 1), (4, 1), (8, 1), (1, 3), (4, 3), (8, 5), (2, 40)))]
+
+
+@pytest.mark.parametrize("kw", PLANS, ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()) or "chosen")
+def test_nan_scores_reach_their_rows_in_every_launch_shape(kw):
+    """A NaN query head poisons its rows, a block of NaN keys (alone in its wavefront's walk or chunk, or beside
+    others) the rows of its kv head, in every partition that covers them; empty ranges stay empty and all other
+    rows keep their bits."""
+    from paper_2510_13223_amd import workloads as W
+    from paper_2510_13223_amd.runner import DeviceWorkload
+
+    lens = [700, 16, 1333, 33, 5]
+    ranges = [[(0, 500), (0, 16), (0, 1300), (0, 17), (0, 0)], [(500, 700), (16, 16), (1300, 1333), (17, 33), (0, 5)]]
+    w = W.make_custom(61, 5, 8, 2, lens, ranges, q_scale=1 / math.sqrt(128))
+    dw = DeviceWorkload(w, **kw)
+
+    def results():
+        dw.run_checked()
+        torch.cuda.synchronize()
+        return [t.clone() for t in (dw.out_partials, dw.lses, dw.out, dw.lse_out, dw.fused_out, dw.fused_lse)]
+
+    clean = results()
+    assert all(not torch.isnan(t).any() for t in clean)
+    bad = torch.zeros(5, 8, dtype=torch.bool, device="cuda")
+    bad[0, 3] = bad[3, 7] = bad[4, 0] = True  # query heads
+    for b, h in bad.nonzero().tolist():
+        dw.q[b, h] = math.nan
+    part_bad = torch.stack([bad, bad])
+    for b, j, g in ((1, 0, 1), (2, 82, 0), (2, 40, 1)):  # the keys of one block of one kv head
+        dw.k_cache[dw.block_table[b, j].long(), g] = math.nan
+        bad[b, 4 * g:4 * g + 4] = True
+        part_bad[1 if (b, j) == (2, 82) else 0, b, 4 * g:4 * g + 4] = True
+    part_bad &= (dw.kv_end > dw.kv_begin)[:, :, None]
+    for got, want, rows in zip(results(), clean, (part_bad, part_bad, bad, bad, bad, bad)):
+        assert torch.isnan(got[rows]).all()
+        assert torch.equal(got[~rows], want[~rows])
