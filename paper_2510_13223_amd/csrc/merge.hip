@@ -7,8 +7,8 @@
 //   out = sum_p w_p out_p / sum_p w_p,  lse_out = M + ln sum_p w_p,
 // skipping parts with lse_p = -inf (their out_p never enters a sum); no live part
 // gives out = 0, lse_out = -inf.  A NaN lse is not in M but has a NaN weight, so
-// a row is empty where its weights sum to 0 and not where M is -inf: a row with
-// parts whose lse is NaN, and no others, is NaN.
+// a row is empty where it has no live part (its weights sum to 0) and not where
+// M is -inf: a row with parts whose lse is NaN, and no others, is NaN.
 //
 // HBM-bound.  32 consecutive threads cover one 128-float row (16 bytes each,
 // one coalesced 512-byte access per part).  Three kernels:
@@ -102,10 +102,20 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const float* __restrict_
     }
   }
   float M = -INFINITY;
+  bool empty = true;
 #pragma unroll
-  for (int p = 0; p < NP; ++p)
-    if (p < n_parts) M = fmaxf(M, l[p]);
+  for (int p = 0; p < NP; ++p) {
+    if (p < n_parts) {
+      M = fmaxf(M, l[p]);
+      empty &= l[p] == -INFINITY;
+    }
+  }
   f32x4* dst = reinterpret_cast<f32x4*>(out + orow * 128) + d4;
+  if (empty) {
+    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (lse_out != nullptr && d4 == 0) lse_out[orow] = -INFINITY;
+    return;
+  }
   float wsum = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -116,14 +126,13 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const float* __restrict_
       acc += w * o[p];
     }
   }
-  if (wsum == 0.f) {
-    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (lse_out != nullptr && d4 == 0) lse_out[orow] = -INFINITY;
-    return;
-  }
   *dst = acc * (1.0f / wsum);
   if (lse_out != nullptr && d4 == 0) lse_out[orow] = M + logf(wsum);
 }
+
+// 1 / the sum of a row's weights; 0 for an empty row, whose sums are 0.  A select costs a short merge
+// less than a branch on the sum (32 rows of 32 parts 3.18 against 3.26 us).
+__device__ __forceinline__ float inverse_sum(float wsum) { return wsum == 0.f ? 0.f : 1.0f / wsum; }
 
 // Any number of parts of many rows.  Group k (of KP) of a row takes parts k, k + KP, ...;
 // its q-th part is p = k + KP q.
@@ -227,26 +236,22 @@ __global__ __launch_bounds__(256) void merge_many_kernel(const float* __restrict
     for (int j = 0; j < KP; ++j) M = fmaxf(M, sm_m[rl * KP + j]);
     acc = f32x4{0.f, 0.f, 0.f, 0.f};
     wsum = 0.f;
+    const float ref = M == -INFINITY ? 0.f : M;
 #pragma unroll
     for (int j = 0; j < KP; ++j) {
-      const float mj = sm_m[rl * KP + j];
-      const float s = mj == M ? 1.f : expf(mj - M);  // 0 for a group of empty parts, whose sums are 0 (or NaN)
+      const float s = expf(sm_m[rl * KP + j] - ref);  // 0 for a group of empty parts, whose sums are 0 (or NaN)
       acc += s * sm_acc[(rl * KP + j) * 32 + d4];
       wsum += s * sm_w[rl * KP + j];
     }
   }
   if (!live) return;
   f32x4* dst = reinterpret_cast<f32x4*>(out + dst_row * 128) + d4;
-  if (wsum == 0.f) {
-    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (lse_out != nullptr && d4 == 0) lse_out[dst_row] = -INFINITY;
-    return;
-  }
+  const float inv = inverse_sum(wsum);
   // Many rows: stored past the caches, so that the launch does not end with them dirty in the L2s
   // (fine's 32,768 rows, 16.8 MB: 2 us of 48).
-  if (KP == 1 && !PIECES) __builtin_nontemporal_store(acc * (1.0f / wsum), dst);
-  else *dst = acc * (1.0f / wsum);
-  if (lse_out != nullptr && d4 == 0) lse_out[dst_row] = M + logf(wsum);
+  if (KP == 1 && !PIECES) __builtin_nontemporal_store(acc * inv, dst);
+  else *dst = acc * inv;
+  if (lse_out != nullptr && d4 == 0) lse_out[dst_row] = M + logf(wsum);  // -inf where wsum = 0
 }
 
 // Few rows of more than four parts (the chunks of few sequences, few partitions of a small batch): a
@@ -325,19 +330,15 @@ __global__ __launch_bounds__(32 * KP) void merge_spread_kernel(const float* __re
   f32x4* dst = reinterpret_cast<f32x4*>(out + at.out * 128) + d4;
   acc = f32x4{0.f, 0.f, 0.f, 0.f};
   wsum = 0.f;
+  const float ref = M == -INFINITY ? 0.f : M;
 #pragma unroll
   for (int j = 0; j < KP; ++j) {
-    const float s = sm_m[j] == M ? 1.f : expf(sm_m[j] - M);  // 0 for a group of empty parts, whose sums are 0 (or NaN)
+    const float s = expf(sm_m[j] - ref);  // 0 for a group of empty parts, whose sums are 0 (or NaN)
     acc += s * sm_acc[j * 32 + d4];
     wsum += s * sm_w[j];
   }
-  if (wsum == 0.f) {
-    *dst = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (lse_out != nullptr && d4 == 0) lse_out[at.out] = -INFINITY;
-    return;
-  }
-  *dst = acc * (1.0f / wsum);
-  if (lse_out != nullptr && d4 == 0) lse_out[at.out] = M + logf(wsum);
+  *dst = acc * inverse_sum(wsum);
+  if (lse_out != nullptr && d4 == 0) lse_out[at.out] = M + logf(wsum);  // -inf where wsum = 0
 }
 
 template <int KP>
