@@ -278,7 +278,8 @@ bana_status bana_decode_attn_fused_copies(const bana_dims* d, const void* q, con
  * Rows of parts with lse = -inf never enter a sum: they may hold anything,
  * NaN included (they lie inside the buffer and may be loaded).  A part with
  * a NaN lse is in J and makes its row NaN, lse_out included.  Summation
- * runs in an order fixed by n_parts alone, so results are deterministic.
+ * runs in an order fixed by n_parts and the number of rows, so results are
+ * deterministic.
  * Of d, only batch, num_q_heads and head_dim are read.
  *   out_partials fp32 [n_parts][batch][num_q_heads][head_dim]
  *   lses         fp32 [n_parts][batch][num_q_heads]

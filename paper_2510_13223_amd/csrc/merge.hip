@@ -337,6 +337,20 @@ __global__ __launch_bounds__(32 * KP) void merge_spread_kernel(const float* __re
     acc += s * sm_acc[j * 32 + d4];
     wsum += s * sm_w[j];
   }
+  // An infinite element times a weight or a rescale that underflowed to 0 is NaN.  Where a sum is not
+  // finite the row is summed again, part after part relative to its own max, and parts of weight 0 are
+  // left out, as merge_many_kernel does.
+  if (!(fabsf((acc[0] + acc[1]) + (acc[2] + acc[3])) < INFINITY)) {
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    wsum = 0.f;
+    for (int p = 0; p < parts.n; ++p) {
+      const int64_t row = parts.first + p * parts.stride;
+      const float lp = lses[row];
+      const float w = lp == -INFINITY ? 0.f : expf(lp - M);
+      wsum += w;
+      if (w != 0.f) acc += w * reinterpret_cast<const f32x4*>(outs + row * 128)[d4];
+    }
+  }
   *dst = acc * inverse_sum(wsum);
   if (lse_out != nullptr && d4 == 0) lse_out[at.out] = M + logf(wsum);  // -inf where wsum = 0
 }

@@ -89,3 +89,23 @@ def test_nan_scores_reach_their_rows_in_every_launch_shape(kw):
     for got, want, rows in zip(results(), clean, (part_bad, part_bad, bad, bad, bad, bad)):
         assert torch.isnan(got[rows]).all()
         assert torch.equal(got[~rows], want[~rows])
+
+
+@pytest.mark.parametrize("n,B,Hq", [m for m in MERGES if m[0] > 4])
+def test_merge_leaves_out_infinite_rows_of_vanishing_weight(n, B, Hq):
+    """A part whose weight beside the row's largest underflows to 0 leaves no 0 x inf behind, also where its
+    weight within a thread group, or the group's within the row, does not underflow."""
+    g = torch.Generator().manual_seed(n)
+    outs = torch.randn(n, B, Hq, 128, generator=g)
+    lses = torch.rand(n, B, Hq, generator=g)
+    far = torch.arange(n) % 4  # 0 near the row's largest, 1 out of fp32's range, 2 and 3 in two steps of half of it
+    lses -= torch.tensor([0.0, 300.0, 120.0, 60.0])[far][:, None, None]
+    outs[(far == 1) | (far == 2)] = math.inf
+    out, lse = _merge(outs, lses)
+    w = torch.softmax(lses.double(), 0)[..., None]
+    want = (w * torch.where(w > 1e-40, outs.double(), 0.0)).sum(0)
+    assert torch.isfinite(out).all()
+    # fp32: the weights, their products and n sums of values up to top, rounded to 2^-24 each
+    top = outs[torch.isfinite(outs)].abs().max().item()
+    np.testing.assert_allclose(out.double().numpy(), want.numpy(), rtol=0, atol=(n + 8) * 2.0**-24 * top)
+    np.testing.assert_allclose(lse.double().numpy(), torch.logsumexp(lses.double(), 0).numpy(), rtol=0, atol=1e-5)
