@@ -237,12 +237,12 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   int min_chunk = 1;
   bool uncut = !split;  // one workgroup per range, whatever its length
   if (few && split && bound > kUnsplitBlocks) {
-    few_chunks = std::min<int64_t>(few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks));
+    few_chunks = std::min<int64_t>({few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks), kMaxChunks});
     // Without hints the ranges may be uneven: chunks of a sixth of the table's width, within bounds.
     if (!hinted) {
       const int64_t high = d->num_q_heads / d->num_kv_heads == kMaxGroup ? kUnknownChunkHigh4 : kUnknownChunkHigh;
       const int64_t most = std::max<int64_t>(kUnknownChunkLow, std::min<int64_t>(bound / 6, high));
-      const int64_t least = ceil_div(bound, most);
+      const int64_t least = std::min(ceil_div(bound, most), kMaxChunks);
       // Up to half as many more where that fills the last round of one workgroup per CU: even ranges
       // all end together (56 pairs of 1875 blocks in 8, 9, 10 chunks: 140, 142, 160 us).
       if (least > few_chunks) {
@@ -254,7 +254,7 @@ Plan make_plan(const bana_dims* d, bool split = true) {
         // 505, at 16 and 28 blocks: 63, 66, so narrower tables keep 16).
         min_chunk = most >= kUnknownChunkHigh ? (int)(most / 3) : kMinUnknownBlocks;
         few_chunks = least;
-        for (int64_t n = least + 1; 2 * n <= 3 * least; ++n)
+        for (int64_t n = least + 1; n <= std::min<int64_t>(3 * least / 2, kMaxChunks); ++n)
           if (fill(n) > fill(few_chunks) + 0.02) few_chunks = n;
       }
     }

@@ -37,6 +37,20 @@ def test_without_hints_chunks_stay_below_a_bound():
         assert _chunks(B, G * Hkv, Hkv, 16 * blocks, 0)[0] == want, (B, Hkv, blocks)
 
 
+def test_planning_a_wide_table_takes_no_longer():
+    """The chunk count is chosen among those that can be launched (at most 256), whatever the table's width."""
+    import time
+
+    wide = bana.make_dims(1, 32, 8, 1 << 26, 100000)
+    ws = bana.lib().bana_decode_attn_workspace_bytes
+    t0 = time.perf_counter()
+    for _ in range(2000):
+        ws(ctypes.byref(wide))
+    assert time.perf_counter() - t0 < 1.0  # some 2 us each; a search over the width's chunks took 2 ms
+    # One pair, chunks of 192 blocks: from 256 chunks' worth on, all 256.
+    assert [_chunks(1, 4, 1, 16 * blocks, 0)[0] for blocks in (49152, 60000, 100000, 131071)] == [256] * 4
+
+
 def test_even_ranges_get_one_workgroup_per_cu():
     for B, Hkv in ((1, 2), (3, 8), (16, 8), (32, 8), (33, 8), (100, 8)):
         n, _ = _chunks(B, 4 * Hkv, Hkv, 100000, 100000 * B)
