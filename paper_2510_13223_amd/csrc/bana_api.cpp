@@ -87,16 +87,42 @@ bana_status check_dims(const bana_dims* d) {
 
 struct Plan {
   int waves;      // wavefronts per workgroup
-  int nc;         // chunks per (sequence, kv head)
+  int nc = 1;     // chunks per (sequence, kv head)
   int cmin;       // minimum blocks per chunk
   bool seq_major; // workgroups in (sequence, chunk) order
   bool balanced;  // equal block intervals per wavefront across sequences
-  int K;          // balanced: wavefronts per kv head
+  int K = 1;      // balanced: wavefronts per kv head
   int kp;         // balanced: thread groups per row of the piece merge
   bool ordered;   // follow the caller's dispatch order (uneven ranges only)
 };
 
 int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Workspace regions of a plan.  Chunked: chunk partials [nc][B][Hq][128] and
+// [nc][B][Hq].  Balanced: piece partials [K + B][Hq][128] and [K + B][Hq],
+// then the block-count prefix sums [B + 1].
+struct WorkspaceLayout {
+  size_t out, lse, prefix, total;
+};
+
+WorkspaceLayout layout_for(const bana_dims* d, const Plan& p) {
+  WorkspaceLayout w{0, 0, 0, 0};
+  size_t rows;
+  if (p.balanced) rows = ((size_t)p.K + d->batch) * d->num_q_heads;
+  else if (p.nc > 1) rows = (size_t)p.nc * d->batch * d->num_q_heads;
+  else return w;
+  w.lse = align256(rows * kHeadDim * sizeof(float));
+  w.total = align256(w.lse + rows * sizeof(float));
+  if (p.balanced) {
+    w.prefix = w.total;
+    w.total = align256(w.prefix + ((size_t)d->batch + 1) * sizeof(int32_t));
+  }
+  return w;
+}
+
+size_t workspace_for(const bana_dims* d, const Plan& p) { return layout_for(d, p).total; }
 
 // Workgroups are (chunk, sequence, kv head) with `waves` wavefronts each.
 // Aim for one full round of resident wavefronts (256 CUs x 16).  With the
@@ -204,10 +230,10 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     // Blocks the wavefronts of the longest chunk walk, and those of the balanced launch.
     const int64_t chunked_walk = bound / (8 * std::max<int64_t>(1, few_groups / active_pairs));
     const int64_t balanced_walk = call_blocks * d->num_kv_heads / kBalancedTargetWaves;
-    // Short calls take it only with slots that the static scratch holds too.
+    // Short calls take it only with a workspace that the static scratch holds too.
     const bool long_call = call_blocks >= (int64_t)kMinBlocksPerWave * p.K;
-    const bool long_or_fits = long_call ||
-                              ((int64_t)p.K + d->batch) * d->num_q_heads * kSlotBytes <= kScratchForSplits;
+    p.balanced = true;
+    const bool long_or_fits = long_call || workspace_for(d, p) <= bana::kStaticScratchBytes;
     p.balanced = d->plan_hint == 2 ||
                  (uneven && few_pairs && long_or_fits &&
                   (chunked_walk >= balanced_walk + kBalancedSaves || balanced_walk >= kBalancedLongWalk ||
@@ -320,32 +346,6 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   if (((int64_t)p.nc * pairs + kMaxSideCopyGroups) * 64 * p.waves > kMaxLaunchItems) p.nc = 1;
   return p;
 }
-
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
-// Workspace regions of a plan.  Chunked: chunk partials [nc][B][Hq][128] and
-// [nc][B][Hq].  Balanced: piece partials [K + B][Hq][128] and [K + B][Hq],
-// then the block-count prefix sums [B + 1].
-struct WorkspaceLayout {
-  size_t out, lse, prefix, total;
-};
-
-WorkspaceLayout layout_for(const bana_dims* d, const Plan& p) {
-  WorkspaceLayout w{0, 0, 0, 0};
-  size_t rows;
-  if (p.balanced) rows = ((size_t)p.K + d->batch) * d->num_q_heads;
-  else if (p.nc > 1) rows = (size_t)p.nc * d->batch * d->num_q_heads;
-  else return w;
-  w.lse = align256(rows * kHeadDim * sizeof(float));
-  w.total = align256(w.lse + rows * sizeof(float));
-  if (p.balanced) {
-    w.prefix = w.total;
-    w.total = align256(w.prefix + ((size_t)d->batch + 1) * sizeof(int32_t));
-  }
-  return w;
-}
-
-size_t workspace_for(const bana_dims* d, const Plan& p) { return layout_for(d, p).total; }
 
 bana_status device_status(hipError_t e) {
   if (e == hipSuccess) return BANA_OK;

@@ -70,6 +70,17 @@ def test_chunk_partials_of_short_calls_fit_the_static_scratch():
                         assert ws <= bana.STATIC_SCRATCH_BYTES, (B, active, Hq, longest, total)
 
 
+def test_short_balanced_launches_fit_the_static_scratch():
+    """A short call of uneven ranges takes the balanced launch only where its whole workspace (piece rows, their lse,
+    the prefix sums and the alignment between them) fits, so the no-allocation call keeps accepting it."""
+    from test_library_abi import _balanced_bytes
+
+    for Hq, Hkv, longest, total in ((64, 4, 8000, 8950), (64, 8, 4000, 4500), (128, 16, 8000, 9000)):
+        need = {B: _chunks(B, Hq, Hkv, longest, total, nonempty_ranges=min(B, 20))[1] for B in range(1, 2049)}
+        assert max(need.values()) <= bana.STATIC_SCRATCH_BYTES, (Hq, Hkv)
+        assert any(ws == _balanced_bytes(B, Hq, Hkv) for B, ws in need.items())
+
+
 GPU_CASES = [
     # B, Hq, Hkv, lengths (cycled), parts
     (1, 4, 1, [256], 1),          # a whole range per workgroup: 16 blocks, 4 wavefronts
