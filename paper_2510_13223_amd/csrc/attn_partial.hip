@@ -406,21 +406,31 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4, 8))) 
   }
   BANA_TIMELINE_MARK(0);
   const unsigned wg = blockIdx.x - a.copies.n_wg;
-  const unsigned bc = a.by_ng.quotient(wg);  // (sequence, chunk)
-  const int g = a.g0 + (int)(wg - bc * a.ng);
-  // Few pairs: a sequence's chunks one after the other, so that the chunks of a long range come as
-  // one run and spread over all CUs (chunk-major, the long range of a batch of short ones lands on
-  // every B-th workgroup and so on the same few CUs of each XCD: 4 sequences, one 15 times as long as
-  // the others, 40 us against 27).  Many pairs: chunk-major, first chunks first.
-  int c = 0, at = (int)bc;
-  if (a.nc > 1) {
-    const unsigned hi = (a.seq_major ? a.by_nc : a.by_B).quotient(bc);
-    const int lo = (int)(bc - hi * (a.seq_major ? a.nc : a.B));
-    c = a.seq_major ? lo : (int)hi;
-    at = a.seq_major ? (int)hi : lo;
+  // Few pairs with range hints: a sequence's chunks one after the other, so that the chunks of a long
+  // range come as one run and spread over all CUs (chunk-major, the long range of a batch of short ones
+  // lands on every B-th workgroup and so on the same few CUs of each XCD: 4 sequences, one 15 times as
+  // long as the others, 40 us against 27).  Else chunk-major, first chunks first: ranges far below the
+  // bound that the chunks were counted for have all their blocks there, and as every nc-th run of
+  // workgroups they would keep a few XCDs busy and the others idle (60 sequences of 128 blocks, 2 kv
+  // heads, a table of 8192, 32 chunks: 118 us against 33).  With few pairs each row of chunks starts 5
+  // pairs further along, so that a long range's chunks do not share an XCD either.
+  int c = 0;
+  unsigned at = a.by_ng.quotient(wg), head = wg - at * a.ng;
+  if (a.nc > 1 && a.seq_major) {
+    const unsigned b = a.by_nc.quotient(at);
+    c = (int)(at - b * a.nc);
+    at = b;
+  } else if (a.nc > 1) {
+    const unsigned pairs = (unsigned)a.B * a.ng;
+    c = (int)a.by_pairs.quotient(wg);
+    unsigned i = wg - c * pairs + c * a.rotate;
+    i -= a.by_pairs.quotient(i) * pairs;
+    at = a.by_ng.quotient(i);
+    head = i - at * a.ng;
   }
+  const int g = a.g0 + (int)head;
   // The dispatch order is a hint: an entry outside [0, B) is clamped, never followed.
-  const int b = a.seq_order != nullptr ? min(max(table_lookup(a.seq_order, 0, 0, at), 0), a.B - 1) : at;
+  const int b = a.seq_order != nullptr ? min(max(table_lookup(a.seq_order, 0, 0, (int)at), 0), a.B - 1) : (int)at;
   const int G = a.G;
   const int hq0 = g * G;
 

@@ -37,7 +37,12 @@ constexpr int kFewUnevenGroups = 768;  // where the longest is less than twice t
 constexpr int kFewLongGroups = 1024;   // four times the mean, six beyond
 constexpr int kFewRaggedGroups = 1536;
 constexpr int kMinChunkBlocks = 4;     // of the longest range's chunks
-constexpr int kMinUnknownBlocks = 16;  // of a chunk without range hints, tables of some hundred blocks
+constexpr int kMinUnknownBlocks = 16;  // of a chunk without range hints, tables of some hundred blocks,
+constexpr int kUnknownSomePairs = 96;  // from this many pairs on also in narrower ones;
+constexpr int kUnknownWideChunk = 160; // a table is wide (960 blocks) where a sixth of it reaches this:
+constexpr int kMinWideBlocks = 64;     // no shorter chunks there, and from this many pairs on the
+constexpr int kUnknownBalancedPairs = 40;  // balanced launch if it fits
+constexpr int kRowRotation = 5;        // odd: consecutive rows of chunks start on different XCDs
 constexpr int kMinUnevenBlocks = 12;   // (block, kv head) units per workgroup on the mean: less than
 constexpr int kMinLongBlocks = 5;      // twice the mean, beyond
 constexpr int kLongChunkBlocks = 48;   // uneven chunks from here on get 8 wavefronts
@@ -89,7 +94,8 @@ struct Plan {
   int waves;      // wavefronts per workgroup
   int nc = 1;     // chunks per (sequence, kv head)
   int cmin;       // minimum blocks per chunk
-  bool seq_major; // workgroups in (sequence, chunk) order
+  bool seq_major; // workgroups in (sequence, chunk) order; else chunk by chunk,
+  int rotate;     // each row of chunks starting this many pairs after the one before
   bool balanced;  // equal block intervals per wavefront across sequences
   int K = 1;      // balanced: wavefronts per kv head
   int kp;         // balanced: thread groups per row of the piece merge
@@ -157,13 +163,20 @@ size_t workspace_for(const bana_dims* d, const Plan& p) { return layout_for(d, p
 //   64 / 8                 12 log-normal around 6000 (balanced)    71.5 -> 66
 //   28 / 4                 16 log-normal around 6000 (balanced)    54.5 -> 49
 // Without hints the longest range may hold most of the blocks, so chunks stay below kUnknownChunkHigh
-// blocks (below a sixth of shorter tables), of 8 wavefronts.  Fused calls without hints, us: chunks of up
-// to 512 blocks and 4 wavefronts -> this rule -> chunks half / twice as long:
-//   32 / 8, 23 log-normal, up to 2799 blocks  255 -> 226 -> 229 / 246    50, up to 2555  323 -> 267 -> 272 / 290
-//   32 / 8, 40 log-normal, up to 505 blocks   108 -> 63 -> 64 / 74       23 even of 483  130 -> 115 -> 123 / 117
-//   28 / 4, 60 log-normal, up to 1307 blocks  119 -> 101 -> 104 / 115    64 / 8, 8, up to 3063  135 -> 114 -> 123 / 126
-// (even ranges at two workgroups per CU: 3 % slower or more, at half a workgroup 4 to 20 %; from 1024
-// pairs on the rule for many pairs gives one chunk of as many wavefronts).
+// blocks (below a sixth of shorter tables), of 8 wavefronts, and all ranges may be far below the table's
+// width (a table as wide as the model's context): then most workgroups are empty.  They come chunk by
+// chunk, so that the ones with work start first and spread over all XCDs.  Us per call, chunks of up to
+// 512 blocks and 4 wavefronts -> sequence by sequence -> this rule:
+//   32 / 8, 40 log-normal, up to 471 blocks  79 -> 50 -> 53          60 log-normal, up to 275  46 -> 32 -> 35
+//   32 / 8, 60 of 32 blocks, table of 512    26 -> 39 -> 30          60 of 8 blocks            12 -> 28 -> 17
+//   28 / 4, 60 of 128, table of 512          45 -> 50 -> 50          24 of 32 blocks           16 -> 17 -> 11
+// (two thirds of the chunks take 13 us for the 60 of 8 blocks, but 40 for the 60 up to 275.)  Wide tables
+// take the balanced launch, which has no empty workgroups, from kUnknownBalancedPairs pairs on (8 x 2 pairs
+// of 2048 blocks, table of 8192: 49 us chunked, 54 balanced) and where its workspace fits the static scratch,
+// as the no-allocation call takes it too.  Us per call, the three as above with this rule balanced:
+//   32 / 8, 23 log-normal, up to 3761 blocks  209 -> 138 -> 137      60, up to 1100  42 -> 39 -> 32
+//   32 / 2, 100 of 128 blocks, table of 8192   50 -> 190 -> 53       32 / 8, 24 of 128  39 -> 64 -> 41
+//   28 / 4, 60 of 32 blocks, table of 2048     17 -> 53 -> 23        8 of 2048, table of 8192  90 -> 92 -> 94
 //
 // Balanced launch (batch <= kMaxBalancedBatch): kBalancedTargetWaves
 // wavefronts split over the kv heads, each over an equal interval of the
@@ -175,7 +188,8 @@ size_t workspace_for(const bana_dims* d, const Plan& p) { return layout_for(d, p
 // launch's, or those walk kBalancedLongWalk blocks or more, which makes its
 // merge cheap, or, in a long call, most sequences have no range, whose chunk
 // rows the chunked plan's merge would read all the same (54 of 256 with a
-// range: 73 us and a merge of 6, chunked 78 and 9); or asked for by plan_hint 2.  With even ranges the piece merge
+// range: 73 us and a merge of 6, chunked 78 and 9); or without range hints (above); or asked for by
+// plan_hint 2.  With even ranges the piece merge
 // costs more than the rounding to whole chunks, and with many pairs
 // several dispatch rounds, longest range first, balance by themselves
 // (measured on MI355X, cold caches: mixed's 2048-pair calls 193 / 251 us
@@ -212,9 +226,17 @@ Plan make_plan(const bana_dims* d, bool split = true) {
                                                       : std::min<int64_t>(units / kMinLongBlocks, kFewRaggedGroups);
     few_groups = std::max<int64_t>(kFewEvenGroups, groups);
   }
+  const bool few = d->waves_hint == 0 && d->chunks_hint == 0 && active_pairs < (hinted ? kFewPairs : kFewPairs / 2);
+  // Few pairs without range hints: chunks of at most a sixth of the table's width, within bounds.
+  const int64_t high = d->num_q_heads / d->num_kv_heads == kMaxGroup ? kUnknownChunkHigh4 : kUnknownChunkHigh;
+  const int64_t most = std::max<int64_t>(kUnknownChunkLow, std::min<int64_t>(bound / 6, high));
+  const int64_t least = std::min(ceil_div(bound, most), kMaxChunks);
+  const bool bounded = few && !hinted && bound > kUnsplitBlocks && least > few_groups / active_pairs;
+  const bool wide = bounded && most >= kUnknownWideChunk;
   Plan p;
   p.balanced = false;
   p.seq_major = false;
+  p.rotate = 0;
   // The dispatch order pays off only when ranges are uneven (long ones first, short ones
   // filling the end of the launch); with even or unknown lengths its lookup would add one
   // dependent load to every wavefront's start, so it is skipped.
@@ -237,7 +259,8 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     p.balanced = d->plan_hint == 2 ||
                  (uneven && few_pairs && long_or_fits &&
                   (chunked_walk >= balanced_walk + kBalancedSaves || balanced_walk >= kBalancedLongWalk ||
-                   (2 * active < d->batch && long_call)));
+                   (2 * active < d->batch && long_call))) ||
+                 (wide && active_pairs >= kUnknownBalancedPairs && workspace_for(d, p) <= bana::kStaticScratchBytes);
   }
   if (p.balanced) {
     // Pieces of the row with the most: its blocks over intervals of at least s_lo blocks, plus
@@ -258,31 +281,27 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     p.cmin = 1;
     return p;
   }
-  const bool few = d->waves_hint == 0 && d->chunks_hint == 0 && active_pairs < (hinted ? kFewPairs : kFewPairs / 2);
   int64_t few_chunks = 1;
   int min_chunk = 1;
+  bool seq_major = true;
   bool uncut = !split;  // one workgroup per range, whatever its length
   if (few && split && bound > kUnsplitBlocks) {
     few_chunks = std::min<int64_t>({few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks), kMaxChunks});
-    // Without hints the ranges may be uneven: chunks of a sixth of the table's width, within bounds.
-    if (!hinted) {
-      const int64_t high = d->num_q_heads / d->num_kv_heads == kMaxGroup ? kUnknownChunkHigh4 : kUnknownChunkHigh;
-      const int64_t most = std::max<int64_t>(kUnknownChunkLow, std::min<int64_t>(bound / 6, high));
-      const int64_t least = std::min(ceil_div(bound, most), kMaxChunks);
-      // Up to half as many more where that fills the last round of one workgroup per CU: even ranges
-      // all end together (56 pairs of 1875 blocks in 8, 9, 10 chunks: 140, 142, 160 us).
-      if (least > few_chunks) {
-        auto fill = [&](int64_t n) {
-          return (double)(n * active_pairs) / (kFewEvenGroups * ceil_div(n * active_pairs, kFewEvenGroups));
-        };
-        // Ranges far below the table's width stay in chunks of a third of that (28 log-normal ones of up to
-        // 12509 blocks, group of 16, two kv heads: 349 us at 1 block, 342 so; 50 of up to 2555: 270, 259; 40 of up to
-        // 505, at 16 and 28 blocks: 63, 66, so narrower tables keep 16).
-        min_chunk = most >= kUnknownChunkHigh ? (int)(most / 3) : kMinUnknownBlocks;
-        few_chunks = least;
-        for (int64_t n = least + 1; n <= std::min<int64_t>(3 * least / 2, kMaxChunks); ++n)
-          if (fill(n) > fill(few_chunks) + 0.02) few_chunks = n;
-      }
+    // Without hints ranges may be far below the table's width: they stay in chunks of 8 blocks per
+    // wavefront in wide tables and of 2 in narrower ones, and their chunks come first (partial_attn_kernel).
+    if (bounded || (!hinted && active_pairs >= kUnknownSomePairs)) {
+      min_chunk = wide ? kMinWideBlocks : kMinUnknownBlocks;
+      seq_major = false;
+    }
+    // Up to half as many more chunks where that fills the last round of one workgroup per CU: even
+    // ranges all end together (56 pairs of 1875 blocks in 8, 9, 10 chunks: 140, 142, 160 us).
+    if (bounded) {
+      auto fill = [&](int64_t n) {
+        return (double)(n * active_pairs) / (kFewEvenGroups * ceil_div(n * active_pairs, kFewEvenGroups));
+      };
+      few_chunks = least;
+      for (int64_t n = least + 1; n <= std::min<int64_t>(3 * least / 2, kMaxChunks); ++n)
+        if (fill(n) > fill(few_chunks) + 0.02) few_chunks = n;
     }
     // Few active sequences of a large batch: keep the chunk partials of all of it small.
     few_chunks = std::min<int64_t>(few_chunks, kScratchForSplits / ((int64_t)d->batch * d->num_q_heads * kSlotBytes));
@@ -318,7 +337,8 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   } else if (few) {
     p.nc = (int)few_chunks;
     p.cmin = min_chunk;
-    p.seq_major = true;
+    p.seq_major = seq_major;
+    p.rotate = seq_major ? 0 : kRowRotation;
   } else if (hinted) {
     // (block, kv head) units of the call and the blocks per wavefront if they
     // were spread evenly over one round of resident wavefronts.
@@ -417,9 +437,10 @@ bana_status run_attention(const bana_dims* d, const void* q, const void* k_cache
   a.nc = plan.nc;
   a.cmin = plan.cmin;
   a.seq_major = plan.seq_major;
+  a.rotate = plan.rotate;
   a.by_ng.set((uint32_t)ng);
   a.by_nc.set((uint32_t)plan.nc);
-  a.by_B.set((uint32_t)d->batch);
+  a.by_pairs.set((uint32_t)d->batch * (uint32_t)ng);
   // Workspace partials hold the call's heads only; merged rows go to their place in out / lse.
   a.out_hq = ng * G;
   a.out_h0 = g0 * G;

@@ -75,8 +75,9 @@ struct PartialArgs {
   int g0, ng;  // kv heads [g0, g0 + ng) of this launch
   int nc;    // chunks per (sequence, kv head)
   int cmin;  // minimum blocks per chunk
-  FastDiv by_ng, by_nc, by_B;
-  bool seq_major;  // workgroup order: (sequence, chunk, kv head) instead of (chunk, sequence, kv head)
+  FastDiv by_ng, by_nc, by_pairs;  // pairs: B x ng
+  bool seq_major;  // workgroup order: (sequence, chunk, kv head) instead of (chunk, sequence, kv head),
+  int rotate;      // there each row of chunks starting `rotate` pairs after the one before
   // Destination rows: query head h of sequence b (chunk or piece slot c) goes to row
   // (c * B + b) * out_hq + h - out_h0 of out / lse.  Final output: out_hq = Hq, out_h0 = 0;
   // workspace partials of a kv-head range hold only its heads: out_hq = ng * G, out_h0 = g0 * G.

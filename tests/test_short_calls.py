@@ -34,7 +34,21 @@ def test_short_ranges_are_not_cut():
 def test_without_hints_chunks_stay_below_a_bound():
     for B, G, Hkv, blocks, want in ((40, 4, 8, 505, 8), (23, 4, 8, 2799, 15), (60, 4, 8, 129, 3), (63, 4, 8, 384, 6),
                                     (1, 4, 8, 3750, 64), (28, 16, 2, 1875, 9), (28, 16, 2, 8192, 32)):
-        assert _chunks(B, G * Hkv, Hkv, 16 * blocks, 0)[0] == want, (B, Hkv, blocks)
+        assert _chunks(B, G * Hkv, Hkv, 16 * blocks, 0, plan_hint=1)[0] == want, (B, Hkv, blocks)
+
+
+def test_wide_tables_without_hints_take_the_balanced_launch():
+    """From 960 blocks on, where the pairs leave too few chunks to bound them otherwise and the workspace fits."""
+    from test_library_abi import _balanced_bytes
+
+    balanced = lambda B, Hq, Hkv, blocks, **kw: (
+        _chunks(B, Hq, Hkv, 16 * blocks, 0, **kw)[1] == _balanced_bytes(B, Hq, Hkv))
+    for B, Hq, Hkv in ((23, 32, 8), (100, 32, 2), (63, 64, 8), (500, 4, 1)):
+        assert balanced(B, Hq, Hkv, 960) and balanced(B, Hq, Hkv, 8192) and not balanced(B, Hq, Hkv, 959)
+        assert not balanced(B, Hq, Hkv, 8192, plan_hint=1)
+    assert not balanced(1, 32, 8, 8192) and not balanced(39, 4, 1, 8192) and balanced(40, 4, 1, 8192)
+    assert not balanced(64, 64, 8, 8192)  # 512 pairs
+    assert not balanced(500, 16, 1, 8192, waves_hint=4) and balanced(500, 8, 1, 8192)
 
 
 def test_planning_a_wide_table_takes_no_longer():
@@ -95,6 +109,7 @@ GPU_CASES = [
     (9, 16, 1, [9000, 300, 17, 40, 200, 600, 5, 90, 333], 3),  # beyond, group of 16
     (65, 8, 4, [2064, 1, 255, 256, 257, 15], 1),  # 129 blocks wide: without hints 3 chunks, of 16 blocks at least
     (65, 16, 1, [6200, 30, 1025, 1040], 2),       # likewise 388 blocks, group of 16
+    (40, 4, 2, [16000, 40, 900, 17], 2),          # 1000 blocks wide: without hints balanced, or 7 chunks of 64 at least
 ]
 
 
@@ -108,7 +123,8 @@ def test_short_call_shapes_match_the_oracle(case):
     # Cuts at any token; the ranges cover the sequence, as the helper expects; parts of short ones are empty.
     ranges = [[(L * p // parts, L * (p + 1) // parts) for L in lens] for p in range(parts)]
     w = W.make_custom(900 + case, B, Hq, Hkv, lens, ranges, q_scale=1 / math.sqrt(128))
-    for kw in ({}, {"range_hints": False}, {"order_hints": False, "plan_hint": 1}, {"use_workspace": False}):
+    for kw in ({}, {"range_hints": False}, {"range_hints": False, "plan_hint": 1}, {"order_hints": False, "plan_hint": 1},
+               {"use_workspace": False}):
         _full_parity(w, **kw)
 
 
