@@ -148,8 +148,8 @@ bana_status bana_decode_attn_partial(const bana_dims* d, const void* q, const vo
  * For callers that cannot allocate device memory -- code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation:
  * bana_decode_attn_partial without a caller workspace.  Same arguments (less
- * the workspace), same results bit for bit and same errors as
- * bana_decode_attn_partial given a workspace of
+ * the workspace), same results bit for bit (but see the limit below) and same
+ * errors as bana_decode_attn_partial given a workspace of
  * bana_decode_attn_workspace_bytes(d) bytes.  Where that call would split
  * ranges, the partials live in a static device array of the library,
  * BANA_STATIC_SCRATCH_BYTES (64 MiB) on each device, held from the time the
@@ -159,9 +159,12 @@ bana_status bana_decode_attn_partial(const bana_dims* d, const void* q, const vo
  * address up once (hipGetSymbolAddress).
  *   - Limit: when the launch plan for d needs more workspace than the array
  *     holds (bana_decode_attn_workspace_bytes(d) > BANA_STATIC_SCRATCH_BYTES),
- *     the call returns BANA_ERR_UNSUPPORTED before any launch, and
- *     bana_last_error() names both sizes; use bana_decode_attn_partial with a
- *     workspace of your own for such dims.
+ *     the call runs the plan with as many chunks as the array holds, with the
+ *     same results up to rounding order -- calls of few (sequence, kv head)
+ *     pairs with a range in a large batch, for which a workspace of your own is
+ *     faster.  Where that does not fit either, it returns
+ *     BANA_ERR_UNSUPPORTED before any launch, and bana_last_error() names both
+ *     sizes; use bana_decode_attn_partial with a workspace for such dims.
  *   - Sharing: every call on one device uses the same array and leaves its
  *     partials there.  Nothing in it needs to start at zero, but calls that
  *     may overlap on one device (on different streams with no event between

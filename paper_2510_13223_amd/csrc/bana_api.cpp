@@ -10,6 +10,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <string>
 
 #include "kernels.h"
@@ -33,6 +34,8 @@ constexpr int kMaxChunks = 256;
 constexpr int kFewPairs = 1024;        // below this many active pairs (half without range hints)
 constexpr int kFewEvenGroups = 256;    // workgroups: one per CU for even ranges,
 constexpr int kFewUnknownGroups = 512; // two without range hints; with uneven ranges up to three
+constexpr int kFewSparseGroups = 384;  // one and a half for even ranges with empty ones between them, from
+constexpr int kSparsePairs = 64;       // this many pairs on;
 constexpr int kFewUnevenGroups = 768;  // where the longest is less than twice the mean, four up to
 constexpr int kFewLongGroups = 1024;   // four times the mean, six beyond
 constexpr int kFewRaggedGroups = 1536;
@@ -51,6 +54,11 @@ constexpr int kUnknownChunkHigh = 192; // not below the one nor above the other
 constexpr int kUnknownChunkHigh4 = 256; // (the other where the LDS combine allows 4 wavefronts only)
 constexpr int kUnsplitBlocks = 28;     // ranges of at most this many blocks are not cut,
 constexpr int kShortBlocks = 64;       // and of at most this many (twice without hints) not always
+constexpr int kShortSparseBlocks = 200;  // up to here few ranges among many empty ones stay chunked,
+constexpr int kManyPieces = 256;         // and with more pieces to a row than this where rows are many
+constexpr int kFewMergeRows = 4096;
+constexpr int kSparseWalk = 50;  // 8 wavefronts: a block spared to each pays for the launch of 8 x 50 empty workgroups
+constexpr double kMergePerBlock = 330e3; // chunk rows (bytes) merged in the time 4 wavefronts walk a block
 constexpr int kBalancedSaves = 8;
 constexpr int kBalancedLongWalk = 40;
 constexpr int64_t kSlotBytes = (kHeadDim + 1) * sizeof(float);  // a partial row and its lse
@@ -199,9 +207,25 @@ size_t workspace_for(const bana_dims* d, const Plan& p) { return layout_for(d, p
 // -6 49 / 54, -2 92 / 95, 1 91 / 86, 3 107 / 103, 14 125 / 107; in shorter calls its merge
 // weighs more: 4 21 / 28.
 //
-// split: whether the call has workspace for the plan.  Without it every range
-// stays in one workgroup, which then wants as many wavefronts as it can use.
-Plan make_plan(const bana_dims* d, bool split = true) {
+// Few pairs of a batch with a quarter of its ranges empty or more ("sparse"): the merge reads the chunk rows of the
+// whole batch, and workgroups of empty ranges lie between the others, so that one workgroup per CU in
+// number is not one on each CU.  Even ranges get kFewSparseGroups workgroups; chunks are at most so many
+// that the merge's rows cost about what the last chunk spares the walk (kMergePerBlock, a minimum of
+// walk / n + merge x n); long chunks get 8 wavefronts.  Calls with most ranges empty take the balanced
+// launch, whose merge reads pieces only, where they are long, and where more than two thirds of the
+// chunks fall to that limit.  Us per call, 32 / 8, even ranges of 65536 / 8192 tokens (rule for many pairs;
+// chunks limited by the static scratch alone; this rule):
+//   3 of 64     208, 168, 132    37, 33, 34        12 of 64    571, 751, 489     77, 99, 73
+//   1 of 512    550, 135, 72     83, 34, 32        12 of 1024  637, 1029, 493    146, 145, 80
+//   1 of 2048  1912, 687, 74    281, 99, 42        12 of 4096  857, 1544, 744    407, 200, 197
+//
+// room: the workspace the plan may need.  kNone: every range stays in one workgroup, which then wants as
+// many wavefronts as it can use.  kScratch: chunks of few pairs are limited to what the static scratch
+// holds, for no-allocation calls whose plan does not fit it.
+enum class Room { kAny, kScratch, kNone };
+
+Plan make_plan(const bana_dims* d, Room room = Room::kAny) {
+  const bool split = room != Room::kNone;
   const int64_t pairs = (int64_t)d->batch * d->num_kv_heads;
   const int64_t active = d->nonempty_ranges > 0 ? std::min<int64_t>(d->nonempty_ranges, d->batch) : d->batch;
   const int64_t active_pairs = active * d->num_kv_heads;
@@ -218,7 +242,9 @@ Plan make_plan(const bana_dims* d, bool split = true) {
       hinted ? std::max<int64_t>(1, std::min<int64_t>(bound + 1, d->total_range_tokens / (kBlockSize * active) + 1))
              : bound;
   const bool uneven = hinted && 4 * bound > 5 * mean_blocks;
-  int64_t few_groups = hinted ? kFewEvenGroups : kFewUnknownGroups;
+  const bool sparse = 4 * active < 3 * (int64_t)d->batch;
+  int64_t few_groups = !hinted ? kFewUnknownGroups
+                       : sparse && active_pairs >= kSparsePairs ? kFewSparseGroups : kFewEvenGroups;
   if (uneven) {
     const int64_t units = mean_blocks * active_pairs;
     const int64_t groups = bound < 2 * mean_blocks    ? std::min<int64_t>(units / kMinUnevenBlocks, kFewUnevenGroups)
@@ -233,6 +259,29 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   const int64_t least = std::min(ceil_div(bound, most), kMaxChunks);
   const bool bounded = few && !hinted && bound > kUnsplitBlocks && least > few_groups / active_pairs;
   const bool wide = bounded && most >= kUnknownWideChunk;
+  // Chunks of few pairs: as many as their workgroups, and of these what the merge allows.
+  const int64_t rows = (int64_t)d->batch * d->num_q_heads;
+  const int64_t chunk_bytes = rows * kSlotBytes;
+  const int64_t chunk_limit = std::max<int64_t>(
+      1, sparse && room == Room::kAny ? (int64_t)std::sqrt((double)bound * kMergePerBlock / (double)chunk_bytes)
+                                      : kScratchForSplits / chunk_bytes);
+  int64_t few_chunks = 1;
+  bool limited = false;
+  if (few && bound > kUnsplitBlocks) {
+    few_chunks = std::min<int64_t>({few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks), kMaxChunks});
+    // Up to half as many more than the bound asks for where that fills the last round of one workgroup
+    // per CU: even ranges all end together (56 pairs of 1875 blocks in 8, 9, 10 chunks: 140, 142, 160 us).
+    if (bounded) {
+      auto fill = [&](int64_t n) {
+        return (double)(n * active_pairs) / (kFewEvenGroups * ceil_div(n * active_pairs, kFewEvenGroups));
+      };
+      few_chunks = least;
+      for (int64_t n = least + 1; n <= std::min<int64_t>(3 * least / 2, kMaxChunks); ++n)
+        if (fill(n) > fill(few_chunks) + 0.02) few_chunks = n;
+    }
+    limited = few_chunks > 3 * chunk_limit;
+    few_chunks = std::max<int64_t>(1, std::min<int64_t>(few_chunks, chunk_limit));
+  }
   Plan p;
   p.balanced = false;
   p.seq_major = false;
@@ -252,15 +301,19 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     // Blocks the wavefronts of the longest chunk walk, and those of the balanced launch.
     const int64_t chunked_walk = bound / (8 * std::max<int64_t>(1, few_groups / active_pairs));
     const int64_t balanced_walk = call_blocks * d->num_kv_heads / kBalancedTargetWaves;
-    // Short calls take it only with a workspace that the static scratch holds too.
+    // Short calls of uneven ranges and calls without hints take it only with a workspace that the static
+    // scratch holds too.
     const bool long_call = call_blocks >= (int64_t)kMinBlocksPerWave * p.K;
     p.balanced = true;
-    const bool long_or_fits = long_call || workspace_for(d, p) <= bana::kStaticScratchBytes;
+    const bool fits = workspace_for(d, p) <= bana::kStaticScratchBytes;
     p.balanced = d->plan_hint == 2 ||
-                 (uneven && few_pairs && long_or_fits &&
+                 (uneven && few_pairs && (fits || (long_call && room == Room::kAny)) &&
                   (chunked_walk >= balanced_walk + kBalancedSaves || balanced_walk >= kBalancedLongWalk ||
                    (2 * active < d->batch && long_call))) ||
-                 (wide && active_pairs >= kUnknownBalancedPairs && workspace_for(d, p) <= bana::kStaticScratchBytes);
+                 (few && 2 * active < d->batch && room == Room::kAny &&
+                  (long_call || (limited && bound > kShortSparseBlocks &&
+                                 (std::min<int64_t>(p.K, bound) <= kManyPieces || rows <= kFewMergeRows)))) ||
+                 (wide && active_pairs >= kUnknownBalancedPairs && fits);
   }
   if (p.balanced) {
     // Pieces of the row with the most: its blocks over intervals of at least s_lo blocks, plus
@@ -268,12 +321,12 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     // spread each row's pieces over 8 thread groups; with many rows, one group per row streams
     // best unless a row has very many pieces (measured on MI355X, cold caches: mixed's migrated
     // partition, 8,192 rows, 68 / 69 / 71 / 76 us with 1 / 2 / 4 / 8 groups; long's partitions,
-    // 256 rows, fastest with 8).
+    // 256 rows, fastest with 8; 4,096 rows with 64 pieces or more 0.78 of the time with 8, 8,192 rows
+    // 0.85 to 1.19, 16,384 rows 0.98 to 1.46).
     const int64_t u_lo = hinted ? std::max<int64_t>(1, d->total_range_tokens / kBlockSize) : 1;
     const int64_t s_lo = std::max<int64_t>(1, u_lo / p.K);
     const int64_t pieces = (bound + 1) / s_lo + 2;
-    const int64_t rows = (int64_t)d->batch * d->num_q_heads;
-    p.kp = rows < 4096 ? 8 : pieces >= 64 ? 2 : 1;
+    p.kp = rows < kFewMergeRows ? 8 : pieces >= 64 ? (rows == kFewMergeRows ? 8 : 2) : 1;
   }
   if (p.balanced) {
     p.waves = bana::kBalancedWaves;
@@ -281,38 +334,23 @@ Plan make_plan(const bana_dims* d, bool split = true) {
     p.cmin = 1;
     return p;
   }
-  int64_t few_chunks = 1;
   int min_chunk = 1;
   bool seq_major = true;
   bool uncut = !split;  // one workgroup per range, whatever its length
   if (few && split && bound > kUnsplitBlocks) {
-    few_chunks = std::min<int64_t>({few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks), kMaxChunks});
     // Without hints ranges may be far below the table's width: they stay in chunks of 8 blocks per
     // wavefront in wide tables and of 2 in narrower ones, and their chunks come first (partial_attn_kernel).
     if (bounded || (!hinted && active_pairs >= kUnknownSomePairs)) {
       min_chunk = wide ? kMinWideBlocks : kMinUnknownBlocks;
       seq_major = false;
     }
-    // Up to half as many more chunks where that fills the last round of one workgroup per CU: even
-    // ranges all end together (56 pairs of 1875 blocks in 8, 9, 10 chunks: 140, 142, 160 us).
-    if (bounded) {
-      auto fill = [&](int64_t n) {
-        return (double)(n * active_pairs) / (kFewEvenGroups * ceil_div(n * active_pairs, kFewEvenGroups));
-      };
-      few_chunks = least;
-      for (int64_t n = least + 1; n <= std::min<int64_t>(3 * least / 2, kMaxChunks); ++n)
-        if (fill(n) > fill(few_chunks) + 0.02) few_chunks = n;
-    }
-    // Few active sequences of a large batch: keep the chunk partials of all of it small.
-    few_chunks = std::min<int64_t>(few_chunks, kScratchForSplits / ((int64_t)d->batch * d->num_q_heads * kSlotBytes));
-    few_chunks = std::max<int64_t>(few_chunks, 1);
     // Short ranges are cut only where that spares a wavefront enough blocks to pay for the merge
     // launch, against one workgroup of as many wavefronts as the LDS combine allows: 2 blocks, or 8
     // without hints, where the ranges may be much shorter than the table is wide (16 sequences of 800
     // tokens, 8 heads: 13.3 us, cut in two 13.9; 51 of 635 in 4 partitions, no hints: 46 us, cut 50).
     const int most_waves = d->num_q_heads / d->num_kv_heads == kMaxGroup ? 4 : 8;
     if (bound <= (hinted ? kShortBlocks : 2 * kShortBlocks) &&
-        bound / most_waves - bound / (4 * few_chunks) < (hinted ? 2 : 8)) {
+        bound / most_waves - bound / (4 * few_chunks) < (!hinted ? 8 : sparse ? 3 : 2)) {
       few_chunks = 1;
       uncut = true;
     }
@@ -322,7 +360,8 @@ Plan make_plan(const bana_dims* d, bool split = true) {
   else if (few && bound <= kUnsplitBlocks)
     p.waves = bound <= 16 ? 4 : 8;
   else if (few)
-    p.waves = uncut || ((uneven || !hinted) && bound >= kLongChunkBlocks * few_chunks) ? 8 : 4;
+    p.waves = sparse && kSparseWalk * bound < pairs * few_chunks * few_chunks ? 4
+              : uncut || ((uneven || sparse || !hinted) && bound >= kLongChunkBlocks * few_chunks) ? 8 : 4;
   else if (uneven && bound >= 8 * kMinBlocksPerWave)
     p.waves = 8;
   else
@@ -409,14 +448,15 @@ namespace {
 bana_status run_attention(const bana_dims* d, const void* q, const void* k_cache, const void* v_cache,
                           const int32_t* block_table, const int32_t* kv_range_begin, const int32_t* kv_range_end,
                           int n_parts, int g0, int ng, float* out, float* lse, void* workspace,
-                          size_t workspace_bytes, void* stream, const bana::SideCopies* side = nullptr) {
+                          size_t workspace_bytes, void* stream, const bana::SideCopies* side = nullptr,
+                          Room room = Room::kAny) {
   const int G = d->num_q_heads / d->num_kv_heads;
   bana_dims sub = *d;
   sub.num_kv_heads = ng;
   sub.num_q_heads = ng * G;
-  Plan plan = make_plan(&sub);
+  Plan plan = make_plan(&sub, room);
   const WorkspaceLayout ws = layout_for(&sub, plan);
-  if (ws.total > 0 && (workspace == nullptr || workspace_bytes < ws.total)) plan = make_plan(&sub, false);
+  if (ws.total > 0 && (workspace == nullptr || workspace_bytes < ws.total)) plan = make_plan(&sub, Room::kNone);
 
   bana::PartialArgs a;
   a.q = static_cast<const uint16_t*>(q);
@@ -537,11 +577,12 @@ bana_status bana_decode_attn_partial_noalloc(const bana_dims* d, const void* q, 
   const bana_status st = check_partial_args(d, q, k_cache, v_cache, block_table, seq_lens, kv_range_begin,
                                             kv_range_end, out_partial, lse, nullptr);
   if (st != BANA_OK) return st;
-  // The plan and the workspace it needs are those of bana_decode_attn_partial with a
-  // workspace of bana_decode_attn_workspace_bytes(d) bytes; a plan the static scratch
-  // cannot hold is refused rather than run differently.
+  // The plan of bana_decode_attn_partial with a workspace of bana_decode_attn_workspace_bytes(d) bytes,
+  // or, where the static scratch cannot hold it, the one with as many chunks as it can; refused where
+  // that does not fit either.
   const size_t need = workspace_for(d, make_plan(d));
-  if (need > bana::kStaticScratchBytes) {
+  const Room room = need > bana::kStaticScratchBytes ? Room::kScratch : Room::kAny;
+  if (room == Room::kScratch && workspace_for(d, make_plan(d, room)) > bana::kStaticScratchBytes) {
     g_last_error = "bana_decode_attn_partial_noalloc: the launch plan for these dims needs " + std::to_string(need) +
                    " bytes of scratch, the library's static scratch holds " +
                    std::to_string(bana::kStaticScratchBytes) +
@@ -552,7 +593,7 @@ bana_status bana_decode_attn_partial_noalloc(const bana_dims* d, const void* q, 
   const hipError_t e = bana::static_scratch(&scratch);
   if (e != hipSuccess) return device_status(e);
   return run_attention(d, q, k_cache, v_cache, block_table, kv_range_begin, kv_range_end, 1, 0, d->num_kv_heads,
-                       out_partial, lse, scratch, bana::kStaticScratchBytes, stream);
+                       out_partial, lse, scratch, bana::kStaticScratchBytes, stream, nullptr, room);
 }
 
 bana_status bana_decode_attn_fused(const bana_dims* d, const void* q, const void* k_cache, const void* v_cache,

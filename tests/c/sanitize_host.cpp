@@ -197,6 +197,39 @@ bool valid_status(bana_status s) {
   return s == BANA_OK || s == BANA_ERR_INVALID || s == BANA_ERR_UNSUPPORTED || s == BANA_ERR_DEVICE;
 }
 
+
+// Few sequences with a range in a batch of any size: the no-allocation call accepts them all (its plan,
+// if that of the call with a workspace does not fit, is one that fits the static scratch), and every
+// launch stays inside the scratch or the caller's buffers.
+void few_active_ranges() {
+  for (int32_t B : {2, 64, 500, 1520, 2048, 20000})
+    for (int32_t active : {1, 2, 5, 20, 60})
+      for (int32_t Hkv : {2, 4, 8})
+        for (int32_t G : {4, 8, 16})
+          for (int32_t longest : {600, 8000, 120000})
+            for (int64_t total : {(int64_t)longest * active, (int64_t)longest + 50 * (active - 1)})
+              for (int32_t hint : {0, 1}) {
+                if (active > B) continue;
+                bana_dims d{};
+                d.batch = B, d.num_kv_heads = Hkv, d.num_q_heads = Hkv * G;
+                d.head_dim = 128, d.block_size = 16, d.max_blocks_per_seq = 8192, d.num_blocks = 100000;
+                d.max_range_tokens = longest, d.total_range_tokens = total, d.nonempty_ranges = active;
+                d.plan_hint = hint;
+                ++g_case;
+                g_regions.clear();
+                const size_t rows = (size_t)B * d.num_q_heads;
+                add_region(fake(0), rows * 128 * 2);
+                add_region(fake(3), (size_t)B * 8192 * 4);
+                for (int i : {4, 5, 6}) add_region(fake(i), (size_t)B * 4);
+                add_region(fake(7), rows * 128 * 4);
+                add_region(fake(8), rows * 4);
+                auto I = [&](int i) { return static_cast<const int32_t*>(fake(i)); };
+                auto F = [&](int i) { return static_cast<float*>(fake(i)); };
+                REQUIRE(bana_decode_attn_partial_noalloc(&d, fake(0), fake(1), fake(2), I(3), I(4), I(5), I(6), F(7),
+                                                         F(8), nullptr) == BANA_OK);
+              }
+}
+
 }  // namespace
 
 #ifndef BANA_HOSTCHECK_LIBRARY  // built as a shared library, only the stub launchers are needed
@@ -294,6 +327,7 @@ int main(int argc, char** argv) {
     }
     REQUIRE(bana_status_string(st[0]) != nullptr);
   }
+  few_active_ranges();
   printf("sanitized host sweep: %ld cases, %ld calls accepted, %ld launches checked\n", n_cases, ok_calls,
          g_launches);
   return 0;

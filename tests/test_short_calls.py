@@ -71,17 +71,26 @@ def test_even_ranges_get_one_workgroup_per_cu():
         assert n == max(1, 256 // (B * Hkv)), (B, Hkv)
 
 
-def test_chunk_partials_of_short_calls_fit_the_static_scratch():
-    """Few sequences with a range in a large batch: the no-allocation call keeps accepting them."""
-    for B in (2, 64, 500, 2048, 20000):
-        for active in (1, 2, 5, 60):
-            if active > B:
-                continue
-            for Hq, Hkv in ((8, 2), (64, 8), (128, 8)):
-                for longest in (600, 8000, 120000):
-                    for total in (longest * active, longest + 100 * (active - 1)):
-                        _, ws = _chunks(B, Hq, Hkv, longest, total, nonempty_ranges=active, plan_hint=1)
-                        assert ws <= bana.STATIC_SCRATCH_BYTES, (B, active, Hq, longest, total)
+def test_few_active_ranges_of_a_large_batch_are_cut():
+    """With a workspace the plan does not depend on the static scratch: few long ranges among empty ones take the
+    balanced launch, and where that is not wanted or possible as many chunks as their merge pays for.  (That the
+    no-allocation call accepts them all is checked by tests/c/sanitize_host.cpp.)"""
+    from test_library_abi import _balanced_bytes
+
+    for B, Hq, Hkv, active, longest, chunks in (
+            (2048, 32, 8, 4, 120000, 8), (2000, 64, 8, 1, 131072, 6), (1000, 64, 8, 1, 131072, 9),
+            (500, 64, 8, 2, 120000, 12), (256, 64, 8, 1, 65536, 12), (2048, 32, 8, 16, 30000, 3),
+            (4096, 32, 8, 16, 65536, 3), (20000, 8, 2, 1, 120000, 5), (1520, 64, 4, 20, 8000, 1)):
+        for spread in (1, 4):  # even ranges, and one long one
+            total = longest * active if spread == 1 else longest + longest * (active - 1) // 8
+            got, ws = _chunks(B, Hq, Hkv, longest, total, nonempty_ranges=active)
+            if B <= 2048 and longest > 8000:
+                assert ws == _balanced_bytes(B, Hq, Hkv), (B, active, spread)
+            got, ws = _chunks(B, Hq, Hkv, longest, total, nonempty_ranges=active, plan_hint=1)
+            assert got == chunks or (spread == 4 and got >= chunks), (B, active, spread, got)
+    # without a hint of the total, too
+    d = bana.make_dims(2048, 32, 8, 8192, 100000, nonempty_ranges=2)
+    assert bana.lib().bana_decode_attn_workspace_bytes(ctypes.byref(d)) == _balanced_bytes(2048, 32, 8)
 
 
 def test_short_balanced_launches_fit_the_static_scratch():
@@ -89,7 +98,7 @@ def test_short_balanced_launches_fit_the_static_scratch():
     the prefix sums and the alignment between them) fits, so the no-allocation call keeps accepting it."""
     from test_library_abi import _balanced_bytes
 
-    for Hq, Hkv, longest, total in ((64, 4, 8000, 8950), (64, 8, 4000, 4500), (128, 16, 8000, 9000)):
+    for Hq, Hkv, longest, total in ((64, 4, 8000, 8950), (64, 8, 3200, 3700)):
         need = {B: _chunks(B, Hq, Hkv, longest, total, nonempty_ranges=min(B, 20))[1] for B in range(1, 2049)}
         assert max(need.values()) <= bana.STATIC_SCRATCH_BYTES, (Hq, Hkv)
         assert any(ws == _balanced_bytes(B, Hq, Hkv) for B, ws in need.items())
@@ -110,6 +119,9 @@ GPU_CASES = [
     (65, 8, 4, [2064, 1, 255, 256, 257, 15], 1),  # 129 blocks wide: without hints 3 chunks, of 16 blocks at least
     (65, 16, 1, [6200, 30, 1025, 1040], 2),       # likewise 388 blocks, group of 16
     (40, 4, 2, [16000, 40, 900, 17], 2),          # 1000 blocks wide: without hints balanced, or 7 chunks of 64 at least
+    (300, 8, 2, [4000] + [1] * 74, 2),            # first partition: 4 even ranges among 296 empty ones, in 5 chunks
+    (300, 32, 8, [9000] + [1] * 299, 2),          # one longer one: balanced
+    (5000, 16, 2, [9000] + [1] * 2499, 2),        # 2 in a batch beyond the balanced launch: uncut
 ]
 
 
