@@ -25,6 +25,42 @@ def test_native_checks_leave_host_arguments_to_python():
         bana.bana_merge_partials(torch.zeros(2, 1, 1, 128), torch.zeros(2, 1, 1), cpu)
 
 
+@pytest.fixture
+def without_native(monkeypatch):
+    """Only the C library built, as by `make`: the import of the native module fails."""
+    import sys
+
+    import paper_2510_13223_amd as pkg
+
+    monkeypatch.setattr(bana, "_native", None)
+    monkeypatch.delattr(pkg, "_native", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2510_13223_amd._native", None)
+
+
+def test_binding_works_without_the_native_checks(without_native):
+    with pytest.warns(RuntimeWarning, match="make binding"):
+        n = bana._calls()
+    assert n.merge(1, 2, 3, None, None) is None and bana._calls() is n
+    with pytest.raises(ValueError):
+        bana.bana_merge_partials(torch.zeros(2, 1, 1, 128), torch.zeros(2, 1, 1), torch.zeros(1, 1, 128))
+
+
+@pytest.mark.gpu
+@pytest.mark.filterwarnings("ignore:the native argument checks")
+def test_calls_without_the_native_checks_have_the_same_results(without_native):
+    from paper_2510_13223_amd.runner import DeviceWorkload
+
+    w = W.make_config("tiny", 0)
+    plain = DeviceWorkload(w).results()
+    bana._native = None
+    import sys
+
+    del sys.modules["paper_2510_13223_amd._native"]
+    for a, b in zip(plain, DeviceWorkload(w).results()):
+        assert (a == b).all()
+    assert not isinstance(bana._calls(), bana._PythonChecks)
+
+
 @pytest.mark.gpu
 def test_native_checks_take_good_arguments_and_refuse_bad_ones():
     from paper_2510_13223_amd.runner import DeviceWorkload
