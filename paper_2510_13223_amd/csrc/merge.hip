@@ -16,7 +16,8 @@
 //    partial row is loaded up front, before any of them is used, so the
 //    kernel waits on one round of memory latency;
 //  * more parts of few rows (the chunks of few sequences): a row's parts spread
-//    over enough thread groups that each group takes them in one such round;
+//    over 2 to 16 thread groups of 4 parts a round: one such round up to 64 parts,
+//    further ones beyond (plans make up to 256 chunks);
 //  * more parts of many rows, and the balanced launch's pieces: the 32 lanes of
 //    a row first read 32 parts' lse at once and reduce their max with lane
 //    shuffles, then stream the partial rows with loads that do not depend on
@@ -388,7 +389,8 @@ hipError_t launch_merge(const float* outs, const float* lses, int n_parts, Merge
   }
   // With enough rows to fill the GPU, one thread group per row streams best.
   // With few rows (the chunks of few sequences, few partitions), spread a row's
-  // parts over enough thread groups that each takes them in one round of loads.
+  // parts over enough thread groups that each takes them in one round of loads, up to 64 parts (more
+  // in further rounds).
   // More rows stream better with one group each, the more parts the sooner (us per call, spread /
   // one group: 8,192 rows of 5, 8, 16, 40 parts 6.9 / 6.9, 8.5 / 9.2, 13.5 / 15.2, 39.6 / 32.9; 16,384
   // rows of 5, 16 parts 10.7 / 9.7, 30.9 / 24.6).

@@ -323,12 +323,15 @@ def test_fused_dominant_key_and_all_empty():
         assert np.all(op == 0.0) and np.all(np.isneginf(lp))
 
 
-# (parts, batch, heads): the few-part kernel, and the many-part kernel with 1, 2, 4 and 8 thread
-# groups per row, including more than 32 parts per group (several lse rounds per lane).
-# Many rows take one thread group per row, streaming one part per round: up to 32 parts (one lse
-# round per lane), more than 32, and a row count that leaves the last workgroup partly filled.
+# (parts, batch, heads): the few-part kernel; more parts of few rows, a workgroup per row, with 2, 4, 8 and
+# 16 thread groups, including more parts than one round of loads takes (64 with 16 groups).  Many rows
+# take one thread group per row, streaming one part per round: up to 32 parts (one lse round per
+# lane), more than 32, and row counts that leave the last workgroup partly filled.  Then both sides of
+# every line between the two: 4096 and 8192 rows, 8 and 16 parts.
 @pytest.mark.parametrize("n,B,Hq", [(2, 7, 8), (4, 3, 8), (5, 7, 8), (9, 7, 8), (20, 3, 8), (70, 2, 8),
-                                    (300, 2, 8), (40, 128, 32), (6, 1, 1), (16, 128, 32), (12, 4099, 1)])
+                                    (300, 2, 8), (40, 128, 32), (6, 1, 1), (16, 128, 32), (12, 4099, 1),
+                                    (5, 4099, 1), (12, 8195, 1), (20, 4099, 1), (40, 4099, 1),
+                                    *((n, B, 1) for B in (4095, 4096, 8192, 8193) for n in (7, 8, 16, 17))])
 def test_merge_matches_oracle_merge(n, B, Hq):
     rng = np.random.default_rng(n * 1000 + B)
     outs = rng.standard_normal((n, B, Hq, 128)).astype(np.float32)
