@@ -162,9 +162,10 @@ size_t workspace_for(const bana_dims* d, const Plan& p) { return layout_for(d, p
 // keep HBM as busy as more would).  Uneven ranges are all cut into the same number of chunks too,
 // so that a long range's are not the only ones, but into more: three, four or six workgroups per CU
 // as the longest is less than twice, up to four times or more than four times the mean, as long as
-// a workgroup keeps enough blocks on the mean.  No chunk of the longest range is below kMinChunkBlocks blocks, and ranges of at most
-// kUnsplitBlocks are not cut: there the merge launch costs more than the walk.  Measured on MI355X
-// (HIP graph of 24 calls over three inputs, us per call; the rule for many pairs -> this one):
+// a workgroup keeps enough blocks on the mean.  No chunk of the longest range is below
+// kMinChunkBlocks blocks, and ranges of at most kUnsplitBlocks are not cut: there the merge launch costs
+// more than the walk.  Measured on MI355X (HIP graph of 24 calls over three inputs, us per call; the
+// rule for many pairs -> this one):
 //   32 query / 8 kv heads  1 sequence of 256 / 1500 / 6000 tokens  6.5 -> 5.3, 15.9 -> 8.9, 18.0 -> 11.0
 //                          4 sequences of 700 / 3000               11.5 -> 8.8, 18.5 -> 14
 //                          48 sequences of 800                     33 -> 28
@@ -196,9 +197,9 @@ size_t workspace_for(const bana_dims* d, const Plan& p) { return layout_for(d, p
 // launch's, or those walk kBalancedLongWalk blocks or more, which makes its
 // merge cheap, or, in a long call, most sequences have no range, whose chunk
 // rows the chunked plan's merge would read all the same (54 of 256 with a
-// range: 73 us and a merge of 6, chunked 78 and 9); or without range hints (above); or asked for by
-// plan_hint 2.  With even ranges the piece merge
-// costs more than the rounding to whole chunks, and with many pairs
+// range: 73 us and a merge of 6, chunked 78 and 9); or in a wide table without range hints (above);
+// or few ranges among many empty ones (below); or asked for by plan_hint 2.  With even ranges the piece
+// merge costs more than the rounding to whole chunks, and with many pairs
 // several dispatch rounds, longest range first, balance by themselves
 // (measured on MI355X, cold caches: mixed's 2048-pair calls 193 / 251 us
 // chunked against 214 / 263 us balanced; its 1024-pair head halves 317
@@ -267,7 +268,7 @@ Plan make_plan(const bana_dims* d, Room room = Room::kAny) {
                                       : kScratchForSplits / chunk_bytes);
   int64_t few_chunks = 1;
   bool limited = false;
-  if (few && bound > kUnsplitBlocks) {
+  if (few && split && bound > kUnsplitBlocks) {
     few_chunks = std::min<int64_t>({few_groups / active_pairs, ceil_div(bound, kMinChunkBlocks), kMaxChunks});
     // Up to half as many more than the bound asks for where that fills the last round of one workgroup
     // per CU: even ranges all end together (56 pairs of 1875 blocks in 8, 9, 10 chunks: 140, 142, 160 us).
